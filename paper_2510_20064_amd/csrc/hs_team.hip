@@ -187,6 +187,82 @@ __device__ inline uint64_t* norm_copy(const TeamArgs& A, int c, int rows) {
          (c - 1) * norm_copy_words(A.teams, rows);
 }
 
+// The word at w once it carries tag and SKIP(value bits) is false (bounded as await_word).
+template <typename SKIP>
+__device__ inline uint64_t await_value(const uint64_t* w, uint32_t tag, const TeamArgs& A,
+                                       SKIP skip) {
+  uint64_t v = await_word(w, tag, A);
+  for (uint32_t n = 1; !tainted(v) && skip((uint32_t)(v >> 32)); ++n) {
+    if (n >= A.polls || ((n & 255) == 0 && (uint32_t)get_word(A.fail) == tag)) {
+      put_word(A.fail, word_of(1, tag));
+      return (0xFFFFFFFEull << 32) | kTaint | tag;
+    }
+    __builtin_amdgcn_s_sleep(kPollSleep);
+    v = await_word(w, tag, A);
+  }
+  return v;
+}
+
+// Row sums are taken against offset 0, e_v = exp2(z_v c): in fp32's exponent range a sum is as
+// exact there as against the row's maximum, as long as it neither overflows nor sinks towards
+// the denormals, and the maxima, the offsets and the rescaling of every partial sum fall away
+// (a slice whose terms all underflow adds nothing to a row whose sum is in range). At 2^64 a
+// term's exponent is rounded at 2^-18, the rounding of the logit's own product. A row whose sum
+// is not within [2^-64, 2^64] (masked throughout, NaN, or of logits far from 0) is retried: its
+// folder publishes kRetry for its normaliser, every member then takes its slice's sum again,
+// against an offset from the slice's maximum, and publishes it with the sign bit set (a first
+// sum never has it), the maximum beside it, and the folder folds those.
+__device__ inline bool sum_in_range(float s) {
+  constexpr uint32_t kLo = (127u - 64u) << 23, kHi = (127u + 64u) << 23;
+  return __float_as_uint(s) - kLo <= kHi - kLo;
+}
+constexpr uint32_t kShifted = 0x80000000u;
+constexpr uint32_t kRetry = 0x7FC0FFFFu;  // a NaN; published NaNs are 0x7FC00000
+__device__ inline uint32_t plain_nan(float x) { return x != x ? 0x7FC00000u : __float_as_uint(x); }
+__device__ inline uint64_t word_of_bits(uint32_t x, uint32_t tag) {
+  return ((uint64_t)x << 32) | tag;
+}
+
+// Words of a row of a row set: S slice maxima (with an argmax, or where a sum is shifted), S
+// exp2 sums, S argmaxes. Each kind is contiguous, so that a fold's lanes read whole lines.
+__device__ inline uint64_t* stat_row(const TeamArgs& A, int set, int r, int RM) {
+  return A.stat + ((int64_t)set * RM + r) * A.S * 3;
+}
+
+// Log2 normaliser o + l2 of row rr (o integer-valued, l2 small; retry: the retry mark instead) as
+// an unevaluated sum hi + lo (TwoSum); lane c writes copy c.
+template <int D, int NC>
+__device__ __forceinline__ void publish_norm(const TeamArgs& A, int set, int rr, float o,
+                                             float l2, bool retry, uint32_t tt, int lane) {
+  const float hi = o + l2;
+  const float bb = hi - o;
+  const float lo = (o - (hi - bb)) + (l2 - bb);
+  if (lane < NC) {
+    uint64_t* cw = norm_copy(A, lane, D + 1) + ((int64_t)set * (D + 1) + rr) * 3;
+    put_word(cw, word_of_bits(retry ? kRetry : plain_nan(hi), tt));
+    put_word(cw + 1, word_of_bits(retry ? kRetry : plain_nan(lo), tt));
+  }
+}
+
+// The fold of a retried row: its S shifted sums, each against its own offset.
+template <int D, int NC>
+__device__ __forceinline__ void fold_retried(const TeamArgs& A, int set, int rr, uint32_t tag,
+                                             int lane) {
+  const uint64_t* base = stat_row(A, set, rr, D + 1);
+  float o = -INFINITY, sum = 0.0f;
+  bool lost = false;
+  for (int j = lane; j < A.S; j += 64) {
+    const uint64_t w = await_value(base + A.S + j, tag, A,
+                                   [](uint32_t x) { return (x & kShifted) == 0; });
+    const uint64_t mw = await_word(base + j, tag, A);
+    lost |= tainted(w) || tainted(mw);
+    lse2_combine(o, sum, exp_offset_of(word_f(mw), A.c),
+                 __uint_as_float((uint32_t)(w >> 32) & ~kShifted));
+  }
+  wave_lse(o, sum);
+  publish_norm<D, NC>(A, set, rr, o, log2f(sum), false, tag | taint_bits(__ballot(lost) != 0), lane);
+}
+
 // Fold of row rr of row set `set`: the S slice statistics, two slices per lane per pass
 // (lane j takes slices j, j + 64, ... in order), then the wave. Publishes the row's log2
 // normaliser as hi + lo (in NC copies) and its argmax; writes the argmax and agreement
@@ -196,8 +272,8 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
                                 uint32_t tag, int lane) {
   constexpr int RM = D + 1;
   const int S = A.S;
-  const uint64_t* base = A.stat + ((int64_t)set * RM + rr) * S * 3;
-  float m = -INFINITY, o = -INFINITY, sum = 0.0f;
+  const uint64_t* base = stat_row(A, set, rr, RM);
+  float m = -INFINITY, sum = 0.0f;
   int idx = INT_MAX;
   bool lost = false;
   for (int j0 = 0; j0 < S; j0 += 128) {
@@ -206,50 +282,40 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
     for (int h = 0; h < 2; ++h) {  // issue every load of the pass before waiting on any
       const int j = j0 + lane + 64 * h;
       if (j < S) {
-        w[h][0] = get_word(base + 3 * j);
-        if (NEED_SUM) w[h][1] = get_word(base + 3 * j + 1);
-        if (NEED_ARG) w[h][2] = get_word(base + 3 * j + 2);
+        if (NEED_ARG) w[h][0] = get_word(base + j);
+        if (NEED_SUM) w[h][1] = get_word(base + S + j);
+        if (NEED_ARG) w[h][2] = get_word(base + 2 * S + j);
       }
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int j = j0 + lane + 64 * h;
       if (j < S) {
-        if (tag_of(w[h][0]) != tag) w[h][0] = await_word(base + 3 * j, tag, A);
-        lost |= tainted(w[h][0]);
-        const float ms = word_f(w[h][0]);
         if (NEED_ARG) {
-          if (tag_of(w[h][2]) != tag) w[h][2] = await_word(base + 3 * j + 2, tag, A);
-          lost |= tainted(w[h][2]);
-          argmax_combine(m, idx, ms, word_i(w[h][2]));
-        } else {
-          m = fmaxf(m, ms);
+          if (tag_of(w[h][0]) != tag) w[h][0] = await_word(base + j, tag, A);
+          if (tag_of(w[h][2]) != tag) w[h][2] = await_word(base + 2 * S + j, tag, A);
+          lost |= tainted(w[h][0]) || tainted(w[h][2]);
+          argmax_combine(m, idx, word_f(w[h][0]), word_i(w[h][2]));
         }
         if (NEED_SUM) {
-          if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + 3 * j + 1, tag, A);
+          if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + S + j, tag, A);
           lost |= tainted(w[h][1]);
-          lse2_combine(o, sum, exp_offset_of(ms, A.c), word_f(w[h][1]));
+          sum += word_f(w[h][1]);
         }
       }
     }
   }
-  wave_max<NEED_ARG>(m, idx);
-  if (NEED_SUM) wave_lse(o, sum);
-  const uint32_t tt = tag | taint_bits(__ballot(lost) != 0);
-  uint64_t* nw = A.norm + ((int64_t)set * RM + rr) * 3;
+  if (NEED_ARG) wave_max<true>(m, idx);
+  const bool any_lost = __ballot(lost) != 0;
+  const uint32_t tt = tag | taint_bits(any_lost);
   if (NEED_SUM) {
-    // log2 normaliser o + log2(sum) as an unevaluated sum hi + lo (TwoSum); lane c writes
-    // copy c
-    const float l2 = log2f(sum);
-    const float hi = o + l2;
-    const float bb = hi - o;
-    const float lo = (o - (hi - bb)) + (l2 - bb);
-    if (lane < NC) {
-      uint64_t* cw = norm_copy(A, lane, RM) + ((int64_t)set * RM + rr) * 3;
-      put_word(cw, word_of(hi, tt));
-      put_word(cw + 1, word_of(lo, tt));
-    }
+    sum = wave_sum_f(sum);
+    // the sum's exponent apart: the logarithm then lies in [-1, 0), where its error is smallest
+    publish_norm<D, NC>(A, set, rr, (float)__builtin_amdgcn_frexp_expf(sum),
+                        log2f(__builtin_amdgcn_frexp_mantf(sum)),
+                        !any_lost && !sum_in_range(sum), tt, lane);
   }
+  uint64_t* nw = A.norm + ((int64_t)set * RM + rr) * 3;
   if (lane != 0) return;
   if (NEED_ARG) {
     put_word(nw + 2, word_of(idx, tt));
@@ -295,20 +361,19 @@ __device__ inline ItemPos item_pos(const TeamArgs& A, uint32_t set, int slot, in
 
 // LDS of a team workgroup. Per-thread values of every row are stored transposed, [row][thread],
 // so that one 16-lane group reduces one row (group_read) instead of every wave reducing every
-// row on its own. Slice offsets are double-buffered by item parity: an item's min-sum runs
-// after the statistics of its successor.
-template <int D, bool NEED_ARG, bool PT = false>
+// row on its own.
+constexpr uint32_t kWide = 0x80000000u;
+template <int D, bool NEED_SUM, bool NEED_ARG>
 struct TeamLds {
-  float xt[D + 1][kThreads];                  // per-thread max keys / maxima, then exp2 sums
+  float xs[NEED_SUM ? D + 1 : 1][kThreads];   // per-thread exp2 sums (retry: max keys)
+  float xt[NEED_ARG ? D + 1 : 1][kThreads];   // per-thread maxima
   int xi[NEED_ARG ? D + 1 : 1][kThreads];     // per-thread argmax
-  float xs[PT ? D + 1 : 1][kThreads];         // per-thread exp2 sums against the thread's offset
-  int xo[PT ? D + 1 : 1][kThreads];           // that offset (saturated to int32)
-  float xp[D][kThreads];                      // per-thread min-sums of each drafter
-  float o[2][D + 1];                          // slice offsets exp_offset_of(m, c)
-  float no[2][D + 1];                         // -exp_offset(o): the addend of the exponents
-  float nw[D];     // from the logits: -exp_offset(o_d) - (a_t - a_d), a_x = (o_x - hi_x) - lo_x
-  float dl[D];     // from the logits: a_t - a_d
-  uint32_t wide;   // from the logits: some drafter's |offset| is too large for nw to be exact
+  float xp[NEED_SUM ? D : 1][kThreads];       // per-thread min-sums of each drafter
+  float o[D + 1];  // retry, kept e_v: the slice offset that each row's are taken against
+  float no[D + 1];  // retry: minus the slice offset, then (wide form) minus the row offset
+  float nw[D];     // plain: the exponent addend of drafter d
+  float dl[D];     // wide: a_t - a_d
+  uint32_t form;   // 0: plain; kWide: wide; else the item's rows to retry (bit 2 r)
   float G[D];      // kept e_v: 2^(a_t - a_d)
   float F[D];      // factor of drafter d's group sum: 2^(a_d) (kept e_v), else 2^(a_t)
   uint32_t next;  // a row set of the team's coming items, posted by thread 0
@@ -419,6 +484,27 @@ __device__ inline float min_arith(float a, float b) {
   return r;
 }
 
+// Sum of a thread's terms of one row: two interleaved sums, started from the first terms (no
+// additions of zero).
+template <int E>
+__device__ __forceinline__ float sum_elems(const float (&v)[E]) {
+  float a0 = v[0], a1 = v[1];
+#pragma unroll
+  for (int e = 2; e < E; ++e) {
+    if (e & 1) a1 += v[e];
+    else a0 += v[e];
+  }
+  return a0 + a1;
+}
+
+// 2^(x - lo) of an offset difference x (any magnitude) and a small lo: the integer part of x
+// goes to the exponent, so that the fraction keeps its accuracy.
+__device__ inline float exp2_split(float x, float lo) {
+  if (!(fabsf(x) < 0x1p20f)) return __builtin_amdgcn_exp2f(x - lo);  // 0, infinite or NaN
+  const float n = rintf(x);
+  return ldexpf(__builtin_amdgcn_exp2f((x - n) - lo), (int)n);
+}
+
 // The raw registers of one row made opaque to the compiler: each stage unpacks the logits
 // afresh (two integer operations per pair) instead of the compiler keeping the unpacked
 // floats of a whole item live from one stage to the next, which would not fit in registers.
@@ -431,11 +517,12 @@ __device__ __forceinline__ void launder(Raw& x) {
   __builtin_memcpy(&x, w, 16);
 }
 
-// ---- 1. per-thread max (and lowest argmax) of every row of item q, to LDS ----
-template <int DT, int D, bool NEED_ARG, typename L>
-__device__ __forceinline__ void thread_max(const TeamArgs& A, const ItemPos& q,
-                                           typename Vec<DT>::Raw (&raw)[D + 1], L& sh,
-                                           int t) {
+// ---- 1. per-thread statistics of every row of item q in one pass, to LDS: the exp2 sum (KEPT:
+// the e_v stay in x) and, with NEED_ARG, the max and its lowest index ----
+template <int DT, int D, bool NEED_SUM, bool NEED_ARG, bool KEPT, typename L, typename X>
+__device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q,
+                                             typename Vec<DT>::Raw (&raw)[D + 1], X& x, L& sh,
+                                             int t) {
   constexpr int E = Vec<DT>::kElems;
 #pragma unroll
   for (int r = 0; r <= D; ++r) {
@@ -443,128 +530,78 @@ __device__ __forceinline__ void thread_max(const TeamArgs& A, const ItemPos& q,
     launder(raw[r]);
     float z[E];
     Vec<DT>::unpack(raw[r], z);
-    float m = -INFINITY;
-    int idx = INT_MAX;
+    if (NEED_ARG) {
+      float m = -INFINITY;
+      int idx = INT_MAX;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if (NEED_ARG) {
+      for (int e = 0; e < E; ++e) {
         if (z[e] > m) {
           m = z[e];
           idx = q.vi * E + e;
         }
-      } else {
-        m = fmaxf(m, z[e]);
       }
-    }
-    if (NEED_ARG) {
       // a lane whose logits are all -inf still owns its lowest valid index
       if (idx == INT_MAX && q.vi < A.nvec) idx = q.vi * E;
       sh.xt[r][t] = m;
       sh.xi[r][t] = idx;
-    } else {
-      sh.xt[r][t] = __int_as_float(fkey(m));  // integer key: the group max needs no NaN care
     }
-  }
-}
-
-// ---- 1-3. per-thread statistics of every row of item q in one pass (several items per
-// workgroup): the max, the thread's own offset o_t (exp_offset_of: integer-valued, at or
-// above m_t c) and the exp2 sum against it; max keys, sums and offsets to LDS. The offsets
-// are integer-valued, so the group's rescaling of the sums to the slice offset is exact. A
-// thread whose m_t c is -inf (logits all -inf, or finite ones whose product with c is below
-// the fp32 range) takes offset -2^126: each of its logits then gives 0, or NaN for a NaN
-// logit ----
-template <int DT, int D, bool NEED_ARG, typename L>
-__device__ __forceinline__ void thread_stats_pt(const TeamArgs& A, const ItemPos& q,
-                                                typename Vec<DT>::Raw (&raw)[D + 1], L& sh,
-                                                int t) {
-  constexpr int E = Vec<DT>::kElems;
+    if (NEED_SUM) {
+      float v[E];
 #pragma unroll
-  for (int r = 0; r <= D; ++r) {
-    if (r > q.n) continue;
-    launder(raw[r]);
-    float z[E];
-    Vec<DT>::unpack(raw[r], z);
-    float m = -INFINITY;
-    int idx = INT_MAX;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if (NEED_ARG) {
-        if (z[e] > m) {
-          m = z[e];
-          idx = q.vi * E + e;
-        }
-      } else {
-        m = fmaxf(m, z[e]);
+      for (int e = 0; e < E; ++e) {
+        v[e] = __builtin_amdgcn_exp2f(z[e] * A.c);
+        if constexpr (KEPT) x[r][e] = v[e];
       }
+      sh.xs[r][t] = sum_elems(v);
     }
-    // exp_offset_of(m, c) without its test for m c = -inf (no logit whose scaled value is
-    // finite): the fma then gives NaN, which fmaxf replaces by -2^126; every z c - of is then
-    // -inf or far below -2^125, so each e_v is 0 (NaN for a NaN logit); m is never NaN
-    const float mc = m * A.c;
-    const float of = fmaxf(ceilf(fmaf(fabsf(mc), 0x1p-22f, mc)), -0x1p126f);
-    float v[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, -of));
-    float a0 = v[0], a1 = v[1];
-#pragma unroll
-    for (int e = 2; e < E; ++e) {
-      if (e & 1) a1 += v[e];
-      else a0 += v[e];
-    }
-    if (NEED_ARG) {
-      if (idx == INT_MAX && q.vi < A.nvec) idx = q.vi * E;
-      sh.xt[r][t] = m;
-      sh.xi[r][t] = idx;
-    } else {
-      sh.xt[r][t] = __int_as_float(fkey(m));
-    }
-    sh.xs[r][t] = a0 + a1;
-    sh.xo[r][t] = cvt_i32_sat(of);
   }
 }
 
-// ---- 2. group max: 16-lane group gi reduces row gi (every lane of the group gets the slice
-// max m and argmax). Waves whose groups hold no row skip it. ----
-template <int D, bool NEED_ARG, typename L>
-__device__ __forceinline__ void group_max(const L& sh, int n, int gi, int gl, float& m,
-                                          int& idx) {
-  const int r = min(gi, n);  // groups past the last row reduce a copy of it (all 16 lanes
-                             // of a group must take part in the DPP steps)
-  if (NEED_ARG) {
-    float v[16];
-    int iv[16];
-    group_read(&sh.xt[r][0], gl, v);
-    group_read(&sh.xi[r][0], gl, iv);
-    m = v[0];
-    idx = iv[0];
+// ---- 2. row reductions: 16-lane group gi reduces row gi of the LDS rows (groups past the last
+// row reduce a copy of it: all 16 lanes of a group must take part in the DPP steps). Waves whose
+// groups hold no row skip them. ----
+template <typename L>
+__device__ __forceinline__ void group_argmax(const L& sh, int n, int gi, int gl, float& m,
+                                             int& idx) {
+  const int r = min(gi, n);
+  float v[16];
+  int iv[16];
+  group_read(&sh.xt[r][0], gl, v);
+  group_read(&sh.xi[r][0], gl, iv);
+  m = v[0];
+  idx = iv[0];
 #pragma unroll
-    for (int u = 1; u < 16; ++u) argmax_combine(m, idx, v[u], iv[u]);
-    row16_argmax(m, idx);
-  } else {
-    int kv[16];
-    group_read(reinterpret_cast<const int*>(&sh.xt[r][0]), gl, kv);
-    int k = kv[0];
-#pragma unroll
-    for (int u = 1; u < 16; ++u) k = max(k, kv[u]);
-    m = fkey_inv(row16_max(k));
-  }
+  for (int u = 1; u < 16; ++u) argmax_combine(m, idx, v[u], iv[u]);
+  row16_argmax(m, idx);
 }
-
-// Slice statistics of row r as tagged words.
-template <bool NEED_SUM, bool NEED_ARG>
-__device__ __forceinline__ void publish_row(const TeamArgs& A, const ItemPos& q, int r,
-                                            uint32_t tag, float m, float s, int idx, int RM) {
-  uint64_t* wp = A.stat + (((int64_t)q.set * RM + r) * A.S + q.s) * 3;
-  put_word(wp, word_of(m, tag));
-  if (NEED_SUM) put_word(wp + 1, word_of(s, tag));
-  if (NEED_ARG) put_word(wp + 2, word_of(idx, tag));
+template <typename L>
+__device__ __forceinline__ float group_sum(const L& sh, int n, int gi, int gl) {
+  float v[16];
+  group_read(&sh.xs[min(gi, n)][0], gl, v);
+  return row16_sum(sum16(v));
 }
 
 // Slot s's duty index for an item whose duties start at slot rot: duties are numbered from
 // rot on, so that the row and alpha folds move round the team from item to item instead of
 // falling on the same few members every time (the team goes at its slowest member's pace).
 __device__ inline int duty_index(int s, int rot, int S) { return s >= rot ? s - rot : s - rot + S; }
+
+// Reduces and publishes the slice statistics of item q as tagged words.
+template <bool NEED_SUM, bool NEED_ARG, typename L>
+__device__ __forceinline__ void publish_stats(const TeamArgs& A, const ItemPos& q, uint32_t tag,
+                                              int RM, L& sh, int gi, int gl) {
+  float m = 0.0f, s = 0.0f;
+  int idx = 0;
+  if (NEED_ARG) group_argmax(sh, q.n, gi, gl, m, idx);
+  if (NEED_SUM) s = group_sum(sh, q.n, gi, gl);
+  if (gl != 0 || gi > q.n) return;
+  uint64_t* wp = stat_row(A, q.set, gi, RM) + q.s;
+  if (NEED_ARG) {
+    put_word(wp, word_of(m, tag));
+    put_word(wp + 2 * A.S, word_of(idx, tag));
+  }
+  if (NEED_SUM) put_word(wp + A.S, word_of(fabsf(s), tag));  // (a NaN's sign)
+}
 
 // ---- 4. fold duty: rows i, i + S, ... of the row set (i = the slot's duty index for the
 // item's rotation rot), spread over the waves, wave `first` taking the first ----
@@ -576,77 +613,142 @@ __device__ __forceinline__ void fold_item(const TeamArgs& A, const ItemPos& q, u
     fold_row<D, NEED_SUM, NEED_ARG, NC>(A, q.set, rr, q.b, q.k, q.sub, tag, lane);
 }
 
-// ---- 5. normalisers (the duty wave; a barrier follows): lanes 2r and 2r + 1 wait for row r's hi and
-// lo; lane 2r forms a_r = (o_r - hi_r) - lo_r and, for a drafter row, the constants of its
-// min-sum to LDS: G and F = 2^(a_r) for kept e_v (6'), else the exponent addend and 2^(a_t) (6).
+// ---- 5. normalisers L = hi + lo (the duty wave; a barrier follows): lanes 2r and 2r + 1 wait for
+// row r's hi and lo; lane 2r forms a_r = (o_r - hi_r) - lo_r, o_r the offset of the row's
+// exponents, and, for a drafter row, the constants of its min-sum to LDS. Differences of the
+// a_r are taken part by part, so that they lose nothing to a large hi.
+// o_r = 0, except after a retry (AGAIN, every normaliser final), where it is the slice's offset
+// with kept e_v and rint(hi_r) in the wide form.
+// KEPT (6'): G = 2^(a_t - a_d) and F = 2^(a_d). Else (6): exponent addend nw = -(a_t - a_d), or
+// the difference itself in the wide form, and F = 2^(a_t).
 // A row with no finite logit folds to hi = -inf, lo = NaN, so its a is NaN: it has no
 // distribution, and F is NaN whenever a_t or a_d is, which makes that drafter's alpha NaN in
-// either form ----
-template <int D, bool KEPT, typename L>
+// every form. ----
+template <int D, bool KEPT, bool AGAIN, typename L>
 __device__ __forceinline__ void await_norms(const TeamArgs& A, const ItemPos& q, uint32_t tag,
-                                            L& sh, int bf, int lane) {
+                                            L& sh, int lane) {
   float h = 0.0f;
   bool lost = false;
   if (lane < 2 * (q.n + 1)) {
     constexpr int NC = KEPT ? kNormCopies : 1;  // the single-item kernel's fold writes copies
-    const uint64_t w =
-        await_word(norm_copy(A, q.s & (NC - 1), D + 1) +
-                       ((int64_t)q.set * (D + 1) + (lane >> 1)) * 3 + (lane & 1),
-                   tag, A);
+    const uint64_t* p = norm_copy(A, q.s & (NC - 1), D + 1) +
+                        ((int64_t)q.set * (D + 1) + (lane >> 1)) * 3 + (lane & 1);
+    const uint64_t w = AGAIN ? await_value(p, tag, A, [](uint32_t x) { return x == kRetry; })
+                             : await_word(p, tag, A);
     h = word_f(w);
     lost = tainted(w);
   }
   const bool any_lost = __ballot(lost) != 0;
-  if (lane == 0) sh.taint = taint_bits(any_lost);
+  const bool row = !(lane & 1) && lane < 2 * (q.n + 1);
+  const uint64_t retry = __ballot(row && __float_as_uint(h) == kRetry);
+  if (lane == 0) {
+    sh.taint = taint_bits(any_lost);
+    sh.form = AGAIN ? kWide : (uint32_t)retry;
+  }
   const float lo = dpp_f<0xB1>(h);  // lane 2r: the lo of row r, from lane 2r + 1
-  const float a = (sh.o[bf][min(lane >> 1, D)] - h) - lo;
-  const float at = lane_f(a, 0);
-  const bool drafter = !(lane & 1) && lane >= 2 && lane < 2 * (q.n + 1);
-  if (drafter) {
-    const int d = (lane >> 1) - 1;
-    const bool undefined = at != at || a != a;
+  float o = 0.0f;
+  if (AGAIN && row) {
     if (KEPT) {
-      sh.G[d] = __builtin_amdgcn_exp2f(at - a);
-      sh.F[d] = undefined ? NAN : __builtin_amdgcn_exp2f(a);
+      o = sh.o[lane >> 1];
     } else {
-      sh.nw[d] = sh.no[bf][d + 1] - (at - a);
-      sh.dl[d] = at - a;
-      sh.F[d] = undefined ? NAN : __builtin_amdgcn_exp2f(at);
+      o = rintf(h);
+      sh.no[lane >> 1] = fabsf(o) < INFINITY ? -o : 0.0f;
     }
   }
-  if (!KEPT) {
-    // nw_d holds the offset and the small difference a_t - a_d in one float: exact enough
-    // (error <= 2^-17) while |offset| <= 128, the case of ordinary logits; beyond that the
-    // min-sums subtract the difference in a second operation
-    const bool wide = __ballot(drafter && fabsf(sh.no[bf][min(lane >> 1, D)]) > 128.0f) != 0;
-    if (lane == 0) sh.wide = wide;
+  const float x = o - h;
+  const float xt = lane_f(x, 0), lot = lane_f(lo, 0);
+  if (row && lane >= 2) {
+    const int d = (lane >> 1) - 1;
+    const float at = xt - lot, a = x - lo;
+    const bool undefined = at != at || a != a;
+    const float diff = (xt - x) - (lot - lo);  // a_t - a_d
+    if (KEPT) {
+      sh.G[d] = __builtin_amdgcn_exp2f(diff);
+      sh.F[d] = undefined ? NAN : exp2_split(x, lo);
+    } else {
+      sh.nw[d] = -diff;
+      if (AGAIN) sh.dl[d] = diff;
+      sh.F[d] = undefined ? NAN : exp2_split(xt, lot);
+    }
   }
 }
 
-// ---- 3. exponentials kept in registers (workgroups with a single item): e_v = exp2(z_v c - o)
-// against the slice offsets (buffer 0) into x, per-thread sums to LDS ----
-template <int DT, int D, typename L>
-__device__ __forceinline__ void thread_exps_kept(const TeamArgs& A, const ItemPos& q,
-                                                 typename Vec<DT>::Raw (&raw)[D + 1],
-                                                 float (&x)[D + 1][Vec<DT>::kElems], L& sh,
-                                                 int t) {
-  constexpr int E = Vec<DT>::kElems;
+// ---- 5'. retry of the rows of item q whose first sum was out of range (form: bit 2 r for row
+// r, uniform): their slice sums again, against the offset of the slice's maximum (exp_offset_of:
+// integer-valued, at or above m c; -inf, and a sum of 0, for a slice with no logit whose scaled
+// value is finite), published with the maximum; then the folds, and all normalisers. The whole
+// workgroup calls this after a barrier, and it ends with one. Every member of the team comes
+// here for the same item, before it waits for any word of a later one, so the waits end. The
+// logits come from memory again (rare rows are not worth registers). KEPT: the rows' e_v in x
+// follow. ----
+template <int DT, int D, bool KEPT, int NC, typename L, typename X>
+__device__ __forceinline__ void retry_item(const TeamArgs& A, const ItemPos& q, uint32_t form,
+                                           uint32_t tag, X& x, L& sh, int t, int first, int rot) {
+  using Vt = Vec<DT>;
+  constexpr int E = Vt::kElems;
+  const int lane = t & 63, wv = t >> 6, gi = t >> 4, gl = t & 15;
+  const bool rows = wv * 4 <= q.n;
+  const bool mine = rows && gi <= q.n && gl == 0 && ((form >> (2 * min(gi, D))) & 1u) != 0;
+  auto load = [&](int r, float (&z)[E]) {
+    const int row = r == 0 ? 0 : q.sub * D + r;
+    const char* p = static_cast<const char*>(A.rows.ptr[row]) +
+                    ((int64_t)q.b * A.rows.sb[row] + (int64_t)q.k * A.rows.sk[row]) * Vt::kBytes;
+    if (q.vi < A.nvec) Vt::load(p, q.vi, A.V, z);
+    else Vt::unpack(Vt::neg_raw(), z);
+  };
+  for (int r = 0; r <= q.n; ++r) {
+    if (((form >> (2 * r)) & 1u) == 0) continue;
+    float z[E];
+    load(r, z);
+    float m = -INFINITY;
 #pragma unroll
-  for (int r = 0; r <= D; ++r) {
-    if (r > q.n) continue;
-    launder(raw[r]);
-    Vec<DT>::unpack(raw[r], x[r]);
-    const float no = sh.no[0][r];
-#pragma unroll
-    for (int e = 0; e < E; ++e) x[r][e] = __builtin_amdgcn_exp2f(fmaf(x[r][e], A.c, no));
-    float a0 = x[r][0], a1 = x[r][1];
-#pragma unroll
-    for (int e = 2; e < E; ++e) {
-      if (e & 1) a1 += x[r][e];
-      else a0 += x[r][e];
-    }
-    sh.xt[r][t] = a0 + a1;
+    for (int e = 0; e < E; ++e) m = fmaxf(m, z[e]);
+    sh.xs[r][t] = __int_as_float(fkey(m));  // integer key: the group max needs no NaN care
   }
+  __syncthreads();
+  float m = 0.0f;
+  if (rows) {
+    int kv[16];
+    group_read(reinterpret_cast<const int*>(&sh.xs[min(gi, q.n)][0]), gl, kv);
+    int k = kv[0];
+#pragma unroll
+    for (int u = 1; u < 16; ++u) k = max(k, kv[u]);
+    m = fkey_inv(row16_max(k));
+    if (gl == 0 && gi <= q.n) {
+      const float o = exp_offset_of(m, A.c);
+      if (KEPT) sh.o[gi] = mine ? o : 0.0f;
+      sh.no[gi] = -exp_offset(o);
+    }
+  }
+  __syncthreads();
+#pragma unroll(KEPT ? D + 1 : 1)
+  for (int r = 0; r <= D; ++r) {
+    if (((form >> (2 * r)) & 1u) == 0) continue;  // (bits past row n are 0)
+    float z[E];
+    load(r, z);
+    const float no = sh.no[r];
+#pragma unroll
+    for (int e = 0; e < E; ++e) z[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, no));
+    if constexpr (KEPT) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[r][e] = z[e];
+    }
+    sh.xs[r][t] = sum_elems(z);
+  }
+  __syncthreads();
+  if (rows) {
+    const float s = group_sum(sh, q.n, gi, gl);
+    if (mine) {
+      uint64_t* wp = stat_row(A, q.set, gi, D + 1) + q.s;
+      put_word(wp, word_of(m, tag));
+      put_word(wp + A.S, word_of_bits(__float_as_uint(s) | kShifted, tag));
+    }
+  }
+  const int order = (wv + kWaves - first) % kWaves;
+  for (int rr = duty_index(q.s, rot, A.S) + order * A.S; rr <= q.n; rr += kWaves * A.S)
+    if ((form >> (2 * rr)) & 1u) fold_retried<D, NC>(A, q.set, rr, tag, lane);
+  if (wv == first) await_norms<D, KEPT, true>(A, q, tag, sh, lane);
+  __syncthreads();
 }
 
 // ---- 6'. per-thread min-sums from kept e_v: min(p_v, q_v) = 2^(a_d) min(e_t,v G, e_d,v) with
@@ -663,33 +765,27 @@ __device__ __forceinline__ void thread_minsums_kept(const ItemPos& q,
     float y[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) y[e] = min_pos(x[0][e] * G, x[d + 1][e]);
-    float a0 = y[0], a1 = y[1];
-#pragma unroll
-    for (int e = 2; e < E; ++e) {
-      if (e & 1) a1 += y[e];
-      else a0 += y[e];
-    }
-    sh.xp[d][t] = a0 + a1;
+    sh.xp[d][t] = sum_elems(y);
   }
 }
 
 // ---- 6. per-thread min-sums, from the logits again: with u_v = z_t,v c - o_t and
 // w_v = z_d,v c - o_d, p_v = 2^(u_v + a_t) and q_v = 2^(w_v + a_d), so
-// min(p_v, q_v) = 2^(a_t) 2^min(u_v, w_v - (a_t - a_d)), and w_v - (a_t - a_d) is one fma
-// z_d,v c + nw_d; one fma, one min, one exp2 and one add per drafter logit. The factor 2^(a_t)
-// is applied to the group sum. Identical rows give nw_d = -o_t, so both operands agree
-// bitwise ----
+// min(p_v, q_v) = 2^(a_t) 2^min(u_v, w_v - (a_t - a_d)), and in the plain form (both o = 0)
+// w_v - (a_t - a_d) is one fma z_d,v c + nw_d; one fma, one min, one exp2 and one add per
+// drafter logit. The factor 2^(a_t) is applied to the group sum. Identical rows give nw_d = 0,
+// so both operands agree bitwise ----
 template <int DT, int D, bool WIDE, typename L>
 __device__ __forceinline__ void thread_minsums_form(const TeamArgs& A, const ItemPos& q,
                                                     typename Vec<DT>::Raw (&raw)[D + 1], L& sh,
-                                                    int bf, int t) {
+                                                    int t) {
   constexpr int E = Vec<DT>::kElems;
   float u[E];
   launder(raw[0]);
   Vec<DT>::unpack(raw[0], u);
-  const float nt = sh.no[bf][0];
+  const float nt = WIDE ? sh.no[0] : 0.0f;
 #pragma unroll
-  for (int e = 0; e < E; ++e) u[e] = fmaf(u[e], A.c, nt);
+  for (int e = 0; e < E; ++e) u[e] = WIDE ? fmaf(u[e], A.c, nt) : u[e] * A.c;
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     if (d >= q.n) continue;
@@ -701,25 +797,17 @@ __device__ __forceinline__ void thread_minsums_form(const TeamArgs& A, const Ite
       const float nw = sh.nw[d];
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        // a slice with no finite logit has every u_v (target) or w_v (drafter) at -inf; nw_d
-        // is then infinite or NaN, and where the other operand becomes NaN it loses to the -inf
+        // (nw_d is NaN or infinite only for a row without a distribution: F is NaN then)
         y[e] = __builtin_amdgcn_exp2f(min_arith(u[e], fmaf(w[e], A.c, nw)));
       }
     } else {
-      // a large offset: the exact residual z c - o_d first, then the difference
-      const float no = sh.no[bf][d + 1], dl = sh.dl[d];
+      // the exact residual z c - o_d first, then the difference
+      const float no = sh.no[d + 1], dl = sh.dl[d];
 #pragma unroll
       for (int e = 0; e < E; ++e)
         y[e] = __builtin_amdgcn_exp2f(fminf(u[e], fmaf(w[e], A.c, no) - dl));
     }
-    // two interleaved sums, started from the first terms (no additions of zero)
-    float a0 = y[0], a1 = y[1];
-#pragma unroll
-    for (int e = 2; e < E; ++e) {
-      if (e & 1) a1 += y[e];
-      else a0 += y[e];
-    }
-    sh.xp[d][t] = a0 + a1;
+    sh.xp[d][t] = sum_elems(y);
   }
 }
 // The form is chosen once per item (uniform), so that each copy of the loop is straight-line
@@ -727,9 +815,9 @@ __device__ __forceinline__ void thread_minsums_form(const TeamArgs& A, const Ite
 template <int DT, int D, typename L>
 __device__ __forceinline__ void thread_minsums(const TeamArgs& A, const ItemPos& q,
                                                typename Vec<DT>::Raw (&raw)[D + 1], L& sh,
-                                               int bf, int t) {
-  if (sh.wide == 0) thread_minsums_form<DT, D, false>(A, q, raw, sh, bf, t);
-  else thread_minsums_form<DT, D, true>(A, q, raw, sh, bf, t);
+                                               int t) {
+  if (sh.form == 0) thread_minsums_form<DT, D, false>(A, q, raw, sh, t);
+  else thread_minsums_form<DT, D, true>(A, q, raw, sh, t);
 }
 
 // ---- 7. alpha of the set's drafters from the slice partials: output d is summed by slot
@@ -859,7 +947,7 @@ template <int DT, int D, bool NEED_SUM, bool NEED_ARG, bool SINGLE>
 __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
   using Raw = typename Vec<DT>::Raw;
   constexpr int RM = D + 1;
-  __shared__ TeamLds<D, NEED_ARG, NEED_SUM && !SINGLE> sh;
+  __shared__ TeamLds<D, NEED_SUM, NEED_ARG> sh;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int gi = t >> 4, gl = t & 15;  // 16-lane group gi reduces row gi; gl: lane in it
   const int S = A.S;
@@ -937,18 +1025,13 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
       const ItemPos q = item_pos(A, set, slot, D);
       __builtin_amdgcn_s_setprio(kCritPrio);
       mask_tail<DT, D>(A, q, nxt);
-      thread_max<DT, D, NEED_ARG>(A, q, nxt, sh, t);
+      thread_stats<DT, D, false, NEED_ARG, false>(A, q, nxt, sh, sh, t);
       if (j >= 1) post_set(j + 1);
       claim(j + 2);
       __syncthreads();
       if (j >= 1) next = sh.next;
       if (next < nsets) fetch_item<DT, D>(A, item_pos(A, next, slot, D), true, sh, nxt);
-      if (wv * 4 <= q.n) {
-        float m;
-        int idx;
-        group_max<D, NEED_ARG>(sh, q.n, gi, gl, m, idx);
-        if (gl == 0 && gi <= q.n) publish_row<false, NEED_ARG>(A, q, gi, tag, m, 0.0f, idx, RM);
-      }
+      if (wv * 4 <= q.n) publish_stats<false, NEED_ARG>(A, q, tag, RM, sh, gi, gl);
       fold_item<D, false, NEED_ARG>(A, q, tag, lane, wv, kDutyWave);
       __builtin_amdgcn_s_setprio(0);
       __syncthreads();  // the LDS rows are free for the next item
@@ -956,47 +1039,16 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
     }
     finish(A, tag, leader, teams, sh, t);
   } else {
-    // statistics of item q from raw (bf: its offset buffer), published
-    auto stats = [&](const ItemPos& q, Raw (&raw)[RM], int bf) __attribute__((always_inline)) {
+    // statistics of item q from raw, published
+    auto stats = [&](const ItemPos& q, Raw (&raw)[RM]) __attribute__((always_inline)) {
       __builtin_amdgcn_s_setprio(kCritPrio);
       mask_tail<DT, D>(A, q, raw);
-      thread_stats_pt<DT, D, NEED_ARG>(A, q, raw, sh, t);
+      thread_stats<DT, D, true, NEED_ARG, false>(A, q, raw, sh, sh, t);
       __syncthreads();
-      if (wv * 4 <= q.n) {  // this wave holds the group of a row
-        float m;
-        int idx;
-        group_max<D, NEED_ARG>(sh, q.n, gi, gl, m, idx);
-        const int r = min(gi, q.n);
-        // -inf for a slice without a logit whose product with c is in range
-        const float o = exp_offset_of(m, A.c);
-        const int os = cvt_i32_sat(exp_offset(o));
-        // the 16 sums of this lane rescaled to the slice offset (exact: powers of two) and
-        // added in sum16's order, four at a time (one 16-byte read of sums and of offsets).
-        // A thread's offset is at most the slice's, unless the thread took offset -2^126 for a
-        // sum that is 0 or NaN. Offsets beyond the int32 range saturate, and a difference that
-        // wraps needs |offset| >= 2^30, where the thread's exponents are all <= -256 and its
-        // sum is exactly 0 (or NaN): ldexp of 0 or NaN is 0 or NaN whatever the shift
-        typedef float F4 __attribute__((ext_vector_type(4)));
-        typedef int I4 __attribute__((ext_vector_type(4)));
-        float c[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const F4 x = *reinterpret_cast<const F4*>(&sh.xs[r][64 * i + 4 * gl]);
-          const I4 y = *reinterpret_cast<const I4*>(&sh.xo[r][64 * i + 4 * gl]);
-          auto d = [&](int yi) { return (int)((uint32_t)yi - (uint32_t)os); };  // wraps
-          c[i] = (ldexpf(x[0], d(y[0])) + ldexpf(x[1], d(y[1]))) +
-                 (ldexpf(x[2], d(y[2])) + ldexpf(x[3], d(y[3])));
-        }
-        const float s = row16_sum((c[0] + c[1]) + (c[2] + c[3]));
-        if (gl == 0 && gi <= q.n) {
-          sh.o[bf][gi] = o;
-          sh.no[bf][gi] = -exp_offset(o);
-          publish_row<true, NEED_ARG>(A, q, gi, tag, m, s, idx, RM);
-        }
-      }
+      if (wv * 4 <= q.n)  // this wave holds the group of a row
+        publish_stats<true, NEED_ARG>(A, q, tag, RM, sh, gi, gl);
       __builtin_amdgcn_s_setprio(0);
     };
-
     // the item's slice partials to the workspace (after a barrier), as tagged words
     auto store_partials = [&](const ItemPos& q) __attribute__((always_inline)) {
       if (wv * 4 < q.n) {
@@ -1045,28 +1097,9 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
       float x[RM][Vec<DT>::kElems];
       __builtin_amdgcn_s_setprio(kCritPrio);
       mask_tail<DT, D>(A, q, R0);
-      thread_max<DT, D, NEED_ARG>(A, q, R0, sh, t);
+      thread_stats<DT, D, true, NEED_ARG, true>(A, q, R0, x, sh, t);
       __syncthreads();
-      const bool rows = wv * 4 <= q.n;
-      float m = 0.0f;
-      int idx = 0;
-      if (rows) {
-        group_max<D, NEED_ARG>(sh, q.n, gi, gl, m, idx);
-        if (gl == 0 && gi <= q.n) {
-          const float o = exp_offset_of(m, A.c);  // -inf: no finite logit in the slice
-          sh.o[0][gi] = o;
-          sh.no[0][gi] = -exp_offset(o);
-        }
-      }
-      __syncthreads();
-      thread_exps_kept<DT, D>(A, q, R0, x, sh, t);
-      __syncthreads();
-      if (rows) {
-        float v[16];
-        group_read(&sh.xt[min(gi, q.n)][0], gl, v);
-        const float sm = row16_sum(sum16(v));
-        if (gl == 0 && gi <= q.n) publish_row<true, NEED_ARG>(A, q, gi, tag, m, sm, idx, RM);
-      }
+      if (wv * 4 <= q.n) publish_stats<true, NEED_ARG>(A, q, tag, RM, sh, gi, gl);
       fold_item<D, true, NEED_ARG, kNormCopies>(A, q, tag, lane, wv, 0);
       __builtin_amdgcn_s_setprio(0);
       // with one item per workgroup the leader counts its team once it has folded row 0 (every
@@ -1074,8 +1107,10 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
       // then overlaps the normaliser wait instead of following the learner step or the alpha
       // folds. (The fold duties start at wave 0, whose thread 0 counts.)
       if (leader && t == 0) count_team(A, tag, teams);
-      if (wv == 0) await_norms<D, true>(A, q, tag, sh, 0, lane);
+      if (wv == 0) await_norms<D, true, false>(A, q, tag, sh, lane);
       __syncthreads();
+      const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
+      if (form) retry_item<DT, D, true, kNormCopies>(A, q, form, tag, x, sh, t, 0, 0);
       thread_minsums_kept<DT, D>(q, x, sh, t);
       __syncthreads();
       store_partials(q);
@@ -1090,7 +1125,7 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
     fetch_item<DT, D>(A, item_pos(A, min(set1, nsets - 1), slot, D), set1 < nsets, sh,
                       R1);
     tag = call_tag(A.epoch);  // first needed once the first loads are in flight
-    stats(q0, R0, 0);
+    stats(q0, R0);
     // the first item's group reductions read every column of the LDS rows that the next
     // item's per-thread statistics overwrite, and nothing else in the first iteration waits
     // for the whole workgroup before those writes (later items are kept apart by the
@@ -1102,7 +1137,6 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
     // holds item j + 1 (loaded). Returns false once the team has no item j + 1.
     auto iter = [&](int j, Raw (&rc)[RM], Raw (&rn)[RM])
                     __attribute__((always_inline)) -> bool {
-      const int bf = j & 1;
       const ItemPos q = item_pos(A, set, slot, D);
       // the leader's claim of item j + 3 goes out before the fold and is posted after it, so
       // waiting for its result waits for nothing else; the duty wave, which folds, claims
@@ -1118,11 +1152,15 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
       if (claiming)
         put_word(mbox + ((j + 3) & 3),
                  mbox_word(block_first((uint32_t)(kB * teams) + cv), j + 3, tag));
-      if (set1 < nsets) stats(item_pos(A, set1, slot, D), rn, bf ^ 1);
+      if (set1 < nsets) stats(item_pos(A, set1, slot, D), rn);
+      else __syncthreads();  // the previous item's constants in LDS are no longer read
       if (set3 == kClaim && t == 0) sh.next = await_mbox(mbox + ((j + 3) & 3), j + 3, tag, A, nsets);
-      if (wv == kDutyWave) await_norms<D, false>(A, q, tag, sh, bf, lane);
+      if (wv == kDutyWave) await_norms<D, false, false>(A, q, tag, sh, lane);
       __syncthreads();
-      thread_minsums<DT, D>(A, q, rc, sh, bf, t);
+      const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
+      if (form)
+        retry_item<DT, D, false, 1>(A, q, form, tag, sh, sh, t, kDutyWave, rotation(set, 0));
+      thread_minsums<DT, D>(A, q, rc, sh, t);
       __syncthreads();
       store_partials(q);
       fetch_item<DT, D>(A, item_pos(A, min(set2, nsets - 1), slot, D), set2 < nsets, sh, rc);
@@ -1194,7 +1232,7 @@ int launch_t(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* learned) {
                   // kernels a workgroup per CU in registers)
     const size_t need = sizeof(double) * (size_t)tail_lds_doubles(A.tail) +
                         sizeof(float) * (size_t)g.N * g.K;
-    if (!NS || need > sizeof(TeamLds<D, NA>)) A.learn = 0;
+    if (!NS || need > sizeof(TeamLds<D, NS, NA>)) A.learn = 0;
   }
   *learned = A.learn != 0;
   A.teams = (int)teams;
