@@ -116,9 +116,10 @@ int validate_eval(const EvalReq& q, hs::TeamGeom* g, hs::RowTable* rows) {
 }
 
 // The one check that asks the device, made after every host-side check: a team of S
-// workgroups must fit on the device at once.
+// workgroups must fit on the device at once (without alpha nothing waits for a team).
 int check_capacity(const EvalReq& q, const hs::TeamGeom& g) {
-  const int cap = hs::team_capacity(g, q.alpha != nullptr, q.agree || q.argmax_t || q.argmax_d);
+  if (!q.alpha) return HS_OK;
+  const int cap = hs::team_capacity(g, q.agree || q.argmax_t || q.argmax_d);
   if (cap < g.S)
     return fail(HS_ERR_LIMIT, "the device holds %d evaluation workgroups at once, %d are needed",
                 cap, g.S);

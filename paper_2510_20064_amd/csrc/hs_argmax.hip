@@ -1,0 +1,269 @@
+// Greedy agreement without alpha: the argmax of every row and, per drafter, whether it equals the
+// target's. Nothing needs a row's normaliser here, so no slice waits for another:
+//   1. the rows of all (query, position) groups, cut into units of 8 KB, form one sequence; a wave
+//      takes a span of it, one unit in registers and the next one's loads in flight, and
+//      publishes the maximum of each row's piece and the vector that holds it, as tagged words;
+//   2. the wave that arrives last at a group folds the group's rows, reads the one vector that
+//      holds each row's maximum for the element, and writes the argmaxes and agreements.
+// Bound by HBM: 64 queries x 8 drafters x 6 positions x 128256 bf16 logits in 142 us (6.2 TB/s; the
+// card streams 7.0). The argmax variant of the team kernel, whose members waited for each other's
+// words between the loads of one item and the next, took 193 us.
+#include <algorithm>
+
+#include "hs_exchange.h"
+
+namespace hs {
+namespace {
+
+constexpr int kStep = 8;  // 16-byte loads of a unit per lane
+// Waves of a launch, when there are units enough: the device holds 4096 to 6144 of them at once, and
+// more and shorter spans only add arrivals (142 us with 4096 and 6144, 153 with 12288).
+constexpr int64_t kMinWaves = 4096;
+
+struct ArgmaxArgs {
+  int N, K, G;
+  int S;     // units per row
+  int span;  // units per wave
+  int total;      // units of all groups
+  int pieces;     // pieces of a row at most
+  FastDiv div_group, divS, divK, div_span;  // by the units of a group, S, K and span
+  int64_t V, nvec;
+  uint32_t* epoch;
+  uint64_t* fail;
+  uint32_t polls;
+  uint64_t* finished;  // groups folded (a tagged count)
+  uint64_t* arrived;   // [G] waves that have published (tagged counts)
+  uint64_t* words;     // [G][N + 1][pieces][2]: maximum, vector
+  int32_t* argmax_t;
+  int32_t* argmax_d;
+  uint8_t* agree;
+  RowTable rows;
+};
+
+template <int DT>
+__device__ __forceinline__ const char* row_ptr(const ArgmaxArgs& A, int r, int g) {
+  const int b = (int)fdiv((uint32_t)g, A.divK), k = g - b * A.K;
+  return static_cast<const char*>(A.rows.ptr[r]) +
+         ((int64_t)b * A.rows.sb[r] + (int64_t)k * A.rows.sk[r]) * Vec<DT>::kBytes;
+}
+
+// Folds group g (one wave, lane r: row r): its pieces' words, then the element of each maximum.
+template <int DT>
+__device__ __forceinline__ void fold_group(const ArgmaxArgs& A, int g, uint32_t tag, int lane) {
+  const int R = A.N + 1;
+  const int b = (int)fdiv((uint32_t)g, A.divK), k = g - b * A.K;
+  int target = -2;
+  for (int r0 = 0; r0 < R; r0 += 64) {
+    const int r = r0 + lane;
+    int e = -2;
+    if (r < R) {
+      const uint32_t u0 = (uint32_t)((g * R + r) * A.S);  // the row's first unit
+      const int n = (int)(fdiv(u0 + (uint32_t)A.S - 1u, A.div_span) - fdiv(u0, A.div_span)) + 1;
+      const uint64_t* w = A.words + ((int64_t)g * R + r) * A.pieces * 2;
+      float m = -INFINITY;
+      int idx = INT_MAX;
+      bool lost = false;
+      for (int j0 = 0; j0 < n; j0 += 4) {
+        uint64_t a[4], c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // issue every load before waiting on any
+          const int i = min(j0 + j, n - 1);
+          a[j] = get_word(w + 2 * i);
+          c[j] = get_word(w + 2 * i + 1);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int i = min(j0 + j, n - 1);
+          if (tag_of(a[j]) != tag || A.polls == 0) a[j] = await_word(w + 2 * i, tag, A);
+          if (tag_of(c[j]) != tag || A.polls == 0) c[j] = await_word(w + 2 * i + 1, tag, A);
+          lost |= tainted(a[j]) || tainted(c[j]);
+          argmax_combine(m, idx, word_f(a[j]), word_i(c[j]));
+        }
+      }
+      if (!lost) e = argmax_element<DT>(row_ptr<DT>(A, r, g), A.V, A.nvec, m, idx);
+    }
+    if (r0 == 0) target = __builtin_amdgcn_readfirstlane(e);
+    if (r < R) {
+      if (r == 0) {
+        if (A.argmax_t) A.argmax_t[(int64_t)b * A.K + k] = e;
+      } else {
+        const int64_t o = ((int64_t)b * A.N + r - 1) * A.K + k;
+        if (A.argmax_d) A.argmax_d[o] = e;
+        if (A.agree) A.agree[o] = (uint8_t)(e == target && e >= 0);
+      }
+    }
+  }
+  if (lane != 0) return;
+  // the last group to be folded advances the epoch; every count is left at 0 for the next tag
+  const uint32_t e0 = *A.epoch;
+  const uint32_t next = tag_of_epoch(e0 + 1u);
+  put_word(A.arrived + g, (uint64_t)next);
+  if (tagged_add(A.finished, tag) == (uint32_t)A.G - 1u) {
+    put_word(A.finished, (uint64_t)next);
+    *A.epoch = e0 + 1u;
+  }
+}
+
+template <int DT>
+__global__ __launch_bounds__(kThreads, 4) void hs_argmax_kernel(ArgmaxArgs A) {
+  using Vt = Vec<DT>;
+  constexpr int E = Vt::kElems;
+  using Raw = typename Vt::Raw;
+  const int lane = threadIdx.x & 63;
+  const int wave = (int)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int u = wave * A.span;
+  const int uend = min(u + A.span, A.total);
+  if (u >= uend) return;
+  // a cached read: the epoch changes only once every wave has arrived, and one agent-scope load
+  // per wave of the same word queues at the memory (some 5 ns each)
+  const uint32_t e0 = *A.epoch;
+  const int R = A.N + 1;
+  const int vfull = (int)(A.V / E);  // complete vectors; a row holds fewer than 2^31 logits
+  // the unit whose loads go out next, and the unit in use
+  int lg = (int)fdiv((uint32_t)u, A.div_group);
+  int lr = (int)fdiv((uint32_t)(u - lg * R * A.S), A.divS);
+  int lc = u - (lg * R + lr) * A.S;
+  const char* lp = row_ptr<DT>(A, lr, lg);
+  int g = lg, r = lr, c = lc;
+  const char* p = lp;
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  typedef const __attribute__((address_space(1))) u4* gp4;
+  // Exactly kStep loads on every path, so that a wait for an older unit leaves these in flight:
+  // every address is clamped into the row's complete vectors (a unit past the span, !valid, reads
+  // the row's last one; a row without any, the workspace's control block). What a clamped load
+  // brings is not used. 16-bit rows load nontemporal (each logit is read once)
+  auto load = [&](Raw (&x)[kStep], bool valid) __attribute__((always_inline)) {
+    // uniform row base + 32-bit lane offset
+    const uint64_t base = reinterpret_cast<uint64_t>(vfull > 0 ? (const void*)lp : A.epoch);
+    const int last = max(vfull - 1, 0), v = valid ? lc * 64 * kStep + lane : last;
+#pragma unroll
+    for (int i = 0; i < kStep; ++i) {
+      const gp4 q = (gp4)(base + (uint32_t)min(v + 64 * i, last) * 16u);
+      const u4 y = DT != HS_F32 ? __builtin_nontemporal_load(q) : *q;
+      __builtin_memcpy(&x[i], &y, 16);
+    }
+    if (++lc == A.S) {
+      lc = 0;
+      if (++lr == R) {
+        lr = 0;
+        ++lg;
+      }
+      lp = row_ptr<DT>(A, lr, min(lg, A.G - 1));
+    }
+  };
+  float best = -INFINITY;
+  int bi = c * 64 * kStep + lane < (int)A.nvec ? c * 64 * kStep + lane : INT_MAX;
+  // uses unit u from x while the loads of the next go out to y; false after the span's last
+  auto step = [&](Raw (&x)[kStep], Raw (&y)[kStep]) __attribute__((always_inline)) -> bool {
+    const bool more = u + 1 < uend;
+    load(y, more);
+    const int v = c * 64 * kStep + lane;
+#pragma unroll
+    for (int i = 0; i < kStep; ++i) {
+      float z[E];
+      Vt::unpack(x[i], z);
+      const float m = max_elems(z);
+      if (m > best && v + 64 * i < vfull) {  // a tie keeps the earlier vector
+        best = m;
+        bi = v + 64 * i;
+      }
+    }
+    const bool row_end = c + 1 == A.S;
+    if (row_end || !more) {
+      // the partial vector at the row's end
+      if (row_end && vfull < (int)A.nvec && (vfull & 63) == lane) {
+        float z[E];
+        Vt::load(p, vfull, A.V, z);
+        const float m = max_elems(z);
+        if (m > best || bi == INT_MAX) {
+          best = m;
+          bi = vfull;
+        }
+      }
+      wave_max<true>(best, bi);
+      const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)tag_of_epoch(e0));
+      const uint32_t first = (uint32_t)((g * R + r) * A.S);  // the row's first unit
+      if (lane == 0) {
+        uint64_t* w = A.words + (((int64_t)g * R + r) * A.pieces +
+                                 (wave - (int)fdiv(first, A.div_span))) * 2;
+        put_word(w, word_of(best, tag));
+        put_word(w + 1, word_of(bi, tag));
+      }
+      if ((row_end && r + 1 == R) || !more) {
+        // arrival: the last of the group's waves folds it. The words carry tags, so the count
+        // needs no ordering against them: one still under way is waited for (bounded)
+        const uint32_t gu = (uint32_t)(g * R * A.S);
+        const uint32_t waves = fdiv(gu + (uint32_t)(R * A.S) - 1u, A.div_span) -
+                               fdiv(gu, A.div_span) + 1u;
+        uint32_t n = 0;
+        if (lane == 0) n = tagged_add(A.arrived + g, tag);
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)n) == waves - 1u)
+          fold_group<DT>(A, g, tag, lane);
+      }
+      best = -INFINITY;
+    }
+    if (!more) return false;
+    ++u;
+    if (row_end) {
+      c = 0;
+      if (++r == R) {
+        r = 0;
+        ++g;
+      }
+      p = row_ptr<DT>(A, r, g);
+      bi = lane < (int)A.nvec ? lane : INT_MAX;
+    } else {
+      ++c;
+    }
+    return true;
+  };
+  Raw x[kStep], y[kStep];
+  load(x, true);
+  for (;;) {  // unrolled by two so that the register buffers alternate without copies
+    if (!step(x, y)) break;
+    if (!step(y, x)) break;
+  }
+}
+
+}  // namespace
+
+int launch_argmax(const TeamGeom& g, const RowTable& rows, uint8_t* agree, int32_t* argmax_t,
+                  int32_t* argmax_d, uint32_t polls, char* ws, hipStream_t stream) {
+  const TeamWs L = team_ws(g);
+  ArgmaxArgs A{};
+  A.N = g.N;
+  A.K = g.K;
+  A.G = g.G;
+  A.V = g.V;
+  A.nvec = g.nvec;
+  const int64_t unit = 64 * kStep;
+  A.S = (int)((g.nvec + unit - 1) / unit);
+  const int64_t per_group = (int64_t)(g.N + 1) * A.S;
+  A.total = (int)(g.G * per_group);
+  A.span = (int)std::max<int64_t>((A.total + kMinWaves - 1) / kMinWaves, 1);
+  A.pieces = (A.S + A.span - 2) / A.span + 1;
+  A.div_group = make_fastdiv((uint32_t)per_group);
+  A.divS = make_fastdiv((uint32_t)A.S);
+  A.divK = make_fastdiv((uint32_t)g.K);
+  A.div_span = make_fastdiv((uint32_t)A.span);
+  A.epoch = reinterpret_cast<uint32_t*>(ws + L.epoch);
+  A.fail = reinterpret_cast<uint64_t*>(ws + L.epoch + 8);
+  A.polls = polls;
+  A.finished = reinterpret_cast<uint64_t*>(ws + L.epoch + 24);
+  // the region of the team kernel's slice words: a row has at most as many pieces
+  // as units, and no more units than slices (a slice is four wave loads), of three words each
+  A.words = reinterpret_cast<uint64_t*>(ws + L.stat);
+  A.arrived = reinterpret_cast<uint64_t*>(ws + L.arrived);
+  A.argmax_t = argmax_t;
+  A.argmax_d = argmax_d;
+  A.agree = agree;
+  A.rows = rows;
+  const int64_t waves = (A.total + A.span - 1) / A.span;
+  const unsigned grid = (unsigned)((waves + kWaves - 1) / kWaves);
+  if (g.dtype == HS_F32) hs_argmax_kernel<HS_F32><<<grid, kThreads, 0, stream>>>(A);
+  else if (g.dtype == HS_F16) hs_argmax_kernel<HS_F16><<<grid, kThreads, 0, stream>>>(A);
+  else hs_argmax_kernel<HS_BF16><<<grid, kThreads, 0, stream>>>(A);
+  return hipGetLastError() == hipSuccess ? HS_OK : HS_ERR_HIP;
+}
+
+}  // namespace hs

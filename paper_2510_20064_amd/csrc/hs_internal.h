@@ -207,6 +207,8 @@ struct TeamWs {
   size_t norm_copy;  // bytes of one copy of them (kNormCopies - 1 more follow the gamma words)
   size_t part;   // [G][N][S] words: per-slice sums of min(p, q_i)
   size_t gw;     // [B][N][K] words: gamma (alpha or agreement) for a learner in the same launch
+  size_t arrived;  // [G] tagged counts of the argmax kernel (a region of their own: a count is
+                   // left with the next call's tag)
   size_t total;
 };
 
@@ -238,6 +240,8 @@ inline TeamWs team_ws(const TeamGeom& g) {
   L.gw = off;
   off = align256(off + 8 * (size_t)g.B * g.N * g.K);
   off += (kNormCopies - 1) * L.norm_copy;  // the normaliser words' other copies
+  L.arrived = off;
+  off = align256(off + 8 * (size_t)g.G);
   L.total = off;
   return L;
 }
@@ -364,7 +368,11 @@ int launch_round(const TeamGeom& g, const RowTable& rows, float c, bool need_sum
                  const TailArgs* tail, hipStream_t stream);
 // Workgroups of the team kernel that one device holds at once for this shape and mode (0 if
 // unknown); the launch needs at least S of them.
-int team_capacity(const TeamGeom& g, bool need_sum, bool need_arg);
+int team_capacity(const TeamGeom& g, bool need_arg);
+// Argmax and agreement without alpha (hs_argmax.hip; advances the workspace epoch too). polls: as
+// set_wait_polls left it.
+int launch_argmax(const TeamGeom& g, const RowTable& rows, uint8_t* agree, int32_t* argmax_t,
+                  int32_t* argmax_d, uint32_t polls, char* ws, hipStream_t stream);
 // Polls before a wait inside the team kernel gives up, for launches after this call (negative:
 // the default; 0: every wait gives up at once).
 void set_wait_polls(int polls);

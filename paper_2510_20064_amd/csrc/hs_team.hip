@@ -33,14 +33,14 @@
 // unchanged.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdio>
 
+#include "hs_exchange.h"
 #include "hs_learner.h"
-#include "hs_wave.h"
 
 namespace hs {
 
-constexpr int kPollSleep = 2;  // s_sleep units (64 clocks) between polls
 constexpr int kCritPrio = 2;   // wave priority of the exchange-critical stages (s_setprio)
 constexpr int kFoldPrio = 3;   // and of the pipelined kernel's row folds, which gate the team
 // The wave that holds no row of the group reductions (16-lane group r reduces row r, so the at
@@ -69,6 +69,7 @@ struct TeamArgs {
   // ---- 128 bytes ----
   int64_t nvec;
   float c;
+  float o;             // integer-valued offset of every first exponent (launch_round)
   FastDiv divNsub;     // by nsub
   uint64_t* fail;      // set, with the call's tag, by the first wait that gives up
   uint32_t polls;      // polls before a wait gives up (0: every wait gives up at once)
@@ -91,63 +92,6 @@ struct TeamArgs {
   RowTable rows;
 };
 
-
-// (a vector load: a scalar one would hold up the kernel-argument loads waited on with it)
-__device__ inline uint32_t call_tag(const uint32_t* epoch) {
-  const uint32_t e =
-      __hip_atomic_load(const_cast<uint32_t*>(epoch), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)tag_of_epoch(e));
-}
-
-// Adds 1 to the count that the word w keeps for the call with this tag and returns the
-// count before (0 for the first add of a call): the word holds (count << 32) | tag, and a
-// word with another tag, from an earlier call or never written, counts as 0. So nothing has
-// to be reset between calls, and whatever a word held before cannot skew this call's count.
-// The call that completes a count leaves the word at (0 << 32) | the next call's tag
-// (count_team), so each add of the next call is a single fetch-and-add, which leaves the tag
-// half alone and costs every adder one round trip however many add at once. An add that
-// finds another tag (the first call on a zeroed workspace) goes on by compare-and-swap: the
-// first exchange replaces the whole word, so its earlier fetch-and-adds on the stale word do
-// not count, and every adder is counted once, by its fetch-and-add or by its exchange.
-__device__ inline uint32_t tagged_add(uint64_t* w, uint32_t tag) {
-  const uint64_t old =
-      __hip_atomic_fetch_add(w, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((uint32_t)old == tag) return (uint32_t)(old >> 32);
-  uint64_t cur = get_word(w);
-  for (;;) {  // each failed exchange means another add succeeded: this ends
-    const uint32_t n = (uint32_t)cur == tag ? (uint32_t)(cur >> 32) : 0u;
-    uint64_t expect = cur;
-    if (__hip_atomic_compare_exchange_strong(w, &expect, ((uint64_t)(n + 1u) << 32) | tag,
-                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT))
-      return n;
-    cur = expect;
-  }
-}
-
-// The word at w once it carries tag (its taint mark, if any, kept). Bounded: after `polls`
-// polls, or as soon as another wait of this call has given up, the value is 0xFFFFFFFE (a NaN
-// as float, -2 as int), tainted; the first wait to give up raises the call's fail flag, so one
-// lost word costs one time-out, not one per wait. polls = 0 (set from the host, to test the
-// failure path) makes every wait give up at once.
-__device__ inline uint64_t await_word(const uint64_t* w, uint32_t tag, const TeamArgs& A) {
-  constexpr uint64_t kLost = (0xFFFFFFFEull << 32) | kTaint;
-  if (A.polls == 0) {
-    put_word(A.fail, word_of(1, tag));
-    return kLost | tag;
-  }
-  uint64_t v = get_word(w);
-  for (uint32_t n = 1; tag_of(v) != tag; ++n) {
-    if (n >= A.polls) {
-      put_word(A.fail, word_of(1, tag));
-      return kLost | tag;
-    }
-    if ((n & 255) == 0 && (uint32_t)get_word(A.fail) == tag) return kLost | tag;
-    __builtin_amdgcn_s_sleep(kPollSleep);
-    v = get_word(w);
-  }
-  return v;
-}
 
 // Mailbox word of a team's item j: the row set in bits 38..63, j mod 64 in bits 32..37, the
 // call's tag below, so neither an earlier item's word in the same ring slot nor an earlier
@@ -187,33 +131,18 @@ __device__ inline uint64_t* norm_copy(const TeamArgs& A, int c, int rows) {
          (c - 1) * norm_copy_words(A.teams, rows);
 }
 
-// The word at w once it carries tag and SKIP(value bits) is false (bounded as await_word).
-template <typename SKIP>
-__device__ inline uint64_t await_value(const uint64_t* w, uint32_t tag, const TeamArgs& A,
-                                       SKIP skip) {
-  uint64_t v = await_word(w, tag, A);
-  for (uint32_t n = 1; !tainted(v) && skip((uint32_t)(v >> 32)); ++n) {
-    if (n >= A.polls || ((n & 255) == 0 && (uint32_t)get_word(A.fail) == tag)) {
-      put_word(A.fail, word_of(1, tag));
-      return (0xFFFFFFFEull << 32) | kTaint | tag;
-    }
-    __builtin_amdgcn_s_sleep(kPollSleep);
-    v = await_word(w, tag, A);
-  }
-  return v;
-}
-
-// Row sums are taken against offset 0, e_v = exp2(z_v c): in fp32's exponent range a sum is as
-// exact there as against the row's maximum, as long as it neither overflows nor sinks towards
-// the denormals, and the maxima, the offsets and the rescaling of every partial sum fall away
-// (a slice whose terms all underflow adds nothing to a row whose sum is in range). At 2^64 a
-// term's exponent is rounded at 2^-18, the rounding of the logit's own product. A row whose sum
-// is not within [2^-64, 2^64] (masked throughout, NaN, or of logits far from 0) is retried: its
-// folder publishes kRetry for its normaliser, every member then takes its slice's sum again,
-// against an offset from the slice's maximum, and publishes it with the sign bit set (a first
-// sum never has it), the maximum beside it, and the folder folds those.
+// Row sums are taken against one fixed offset A.o, e_v = exp2(z_v c - A.o): in fp32's exponent range
+// a sum is as exact there as against the row's maximum, as long as it neither overflows nor sinks
+// towards the denormals, and the maxima, the offsets and the rescaling of every partial sum fall
+// away (a slice whose terms all underflow adds nothing to a row whose sum is in range). A row
+// whose sum is not within [2^-64, 2^100] (masked throughout, NaN, or of logits far from 0) is
+// retried: its folder publishes kRetry for its normaliser, every member then takes its slice's sum
+// again, against an offset from the slice's maximum, and publishes it with the sign bit set (a
+// first sum never has it), the maximum beside it, and the folder folds those. At the lower end
+// 2^17 terms below the normal range are 2^-45 of the sum; at the upper a row of 2^27 such slices
+// would still be finite.
 __device__ inline bool sum_in_range(float s) {
-  constexpr uint32_t kLo = (127u - 64u) << 23, kHi = (127u + 64u) << 23;
+  constexpr uint32_t kLo = (127u - 64u) << 23, kHi = (127u + 100u) << 23;
   return __float_as_uint(s) - kLo <= kHi - kLo;
 }
 constexpr uint32_t kShifted = 0x80000000u;
@@ -267,7 +196,7 @@ __device__ __forceinline__ void fold_retried(const TeamArgs& A, int set, int rr,
 // (lane j takes slices j, j + 64, ... in order), then the wave. Publishes the row's log2
 // normaliser as hi + lo (in NC copies) and its argmax; writes the argmax and agreement
 // outputs. The published words are tainted when any slice word was lost.
-template <int D, bool NEED_SUM, bool NEED_ARG, int NC = 1>
+template <int D, bool NEED_ARG, int NC = 1>
 __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int b, int k, int sub,
                                 uint32_t tag, int lane) {
   constexpr int RM = D + 1;
@@ -283,7 +212,7 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
       const int j = j0 + lane + 64 * h;
       if (j < S) {
         if (NEED_ARG) w[h][0] = get_word(base + j);
-        if (NEED_SUM) w[h][1] = get_word(base + S + j);
+        w[h][1] = get_word(base + S + j);
         if (NEED_ARG) w[h][2] = get_word(base + 2 * S + j);
       }
     }
@@ -297,24 +226,20 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
           lost |= tainted(w[h][0]) || tainted(w[h][2]);
           argmax_combine(m, idx, word_f(w[h][0]), word_i(w[h][2]));
         }
-        if (NEED_SUM) {
-          if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + S + j, tag, A);
-          lost |= tainted(w[h][1]);
-          sum += word_f(w[h][1]);
-        }
+        if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + S + j, tag, A);
+        lost |= tainted(w[h][1]);
+        sum += word_f(w[h][1]);
       }
     }
   }
   if (NEED_ARG) wave_max<true>(m, idx);
   const bool any_lost = __ballot(lost) != 0;
   const uint32_t tt = tag | taint_bits(any_lost);
-  if (NEED_SUM) {
-    sum = wave_sum_f(sum);
-    // the sum's exponent apart: the logarithm then lies in [-1, 0), where its error is smallest
-    publish_norm<D, NC>(A, set, rr, (float)__builtin_amdgcn_frexp_expf(sum),
-                        log2f(__builtin_amdgcn_frexp_mantf(sum)),
-                        !any_lost && !sum_in_range(sum), tt, lane);
-  }
+  sum = wave_sum_f(sum);
+  // the sum's exponent apart: the logarithm then lies in [-1, 0), where its error is smallest
+  publish_norm<D, NC>(A, set, rr, A.o + (float)__builtin_amdgcn_frexp_expf(sum),
+                      log2f(__builtin_amdgcn_frexp_mantf(sum)),
+                      !any_lost && !sum_in_range(sum), tt, lane);
   uint64_t* nw = A.norm + ((int64_t)set * RM + rr) * 3;
   if (lane != 0) return;
   if (NEED_ARG) {
@@ -363,12 +288,12 @@ __device__ inline ItemPos item_pos(const TeamArgs& A, uint32_t set, int slot, in
 // so that one 16-lane group reduces one row (group_read) instead of every wave reducing every
 // row on its own.
 constexpr uint32_t kWide = 0x80000000u;
-template <int D, bool NEED_SUM, bool NEED_ARG>
+template <int D, bool NEED_ARG>
 struct TeamLds {
-  float xs[NEED_SUM ? D + 1 : 1][kThreads];   // per-thread exp2 sums (retry: max keys)
+  float xs[D + 1][kThreads];                     // per-thread exp2 sums (retry: max keys)
   float xt[NEED_ARG ? D + 1 : 1][kThreads];   // per-thread maxima
   int xi[NEED_ARG ? D + 1 : 1][kThreads];     // per-thread argmax
-  float xp[NEED_SUM ? D : 1][kThreads];       // per-thread min-sums of each drafter
+  float xp[D][kThreads];                      // per-thread min-sums of each drafter
   float o[D + 1];  // retry, kept e_v: the slice offset that each row's are taken against
   float no[D + 1];  // retry: minus the slice offset, then (wide form) minus the row offset
   float nw[D];     // plain: the exponent addend of drafter d
@@ -519,7 +444,7 @@ __device__ __forceinline__ void launder(Raw& x) {
 
 // ---- 1. per-thread statistics of every row of item q in one pass, to LDS: the exp2 sum (KEPT:
 // the e_v stay in x) and, with NEED_ARG, the max and its lowest index ----
-template <int DT, int D, bool NEED_SUM, bool NEED_ARG, bool KEPT, typename L, typename X>
+template <int DT, int D, bool NEED_ARG, bool KEPT, typename L, typename X>
 __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q,
                                              typename Vec<DT>::Raw (&raw)[D + 1], X& x, L& sh,
                                              int t) {
@@ -545,15 +470,13 @@ __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q
       sh.xt[r][t] = m;
       sh.xi[r][t] = idx;
     }
-    if (NEED_SUM) {
-      float v[E];
+    float v[E];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        v[e] = __builtin_amdgcn_exp2f(z[e] * A.c);
-        if constexpr (KEPT) x[r][e] = v[e];
-      }
-      sh.xs[r][t] = sum_elems(v);
+    for (int e = 0; e < E; ++e) {
+      v[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, -A.o));
+      if constexpr (KEPT) x[r][e] = v[e];
     }
+    sh.xs[r][t] = sum_elems(v);
   }
 }
 
@@ -587,39 +510,39 @@ __device__ __forceinline__ float group_sum(const L& sh, int n, int gi, int gl) {
 __device__ inline int duty_index(int s, int rot, int S) { return s >= rot ? s - rot : s - rot + S; }
 
 // Reduces and publishes the slice statistics of item q as tagged words.
-template <bool NEED_SUM, bool NEED_ARG, typename L>
+template <bool NEED_ARG, typename L>
 __device__ __forceinline__ void publish_stats(const TeamArgs& A, const ItemPos& q, uint32_t tag,
                                               int RM, L& sh, int gi, int gl) {
-  float m = 0.0f, s = 0.0f;
+  float m = 0.0f;
   int idx = 0;
   if (NEED_ARG) group_argmax(sh, q.n, gi, gl, m, idx);
-  if (NEED_SUM) s = group_sum(sh, q.n, gi, gl);
+  const float s = group_sum(sh, q.n, gi, gl);
   if (gl != 0 || gi > q.n) return;
   uint64_t* wp = stat_row(A, q.set, gi, RM) + q.s;
   if (NEED_ARG) {
     put_word(wp, word_of(m, tag));
     put_word(wp + 2 * A.S, word_of(idx, tag));
   }
-  if (NEED_SUM) put_word(wp + A.S, word_of(fabsf(s), tag));  // (a NaN's sign)
+  put_word(wp + A.S, word_of(fabsf(s), tag));  // (a NaN's sign)
 }
 
 // ---- 4. fold duty: rows i, i + S, ... of the row set (i = the slot's duty index for the
 // item's rotation rot), spread over the waves, wave `first` taking the first ----
-template <int D, bool NEED_SUM, bool NEED_ARG, int NC = 1>
+template <int D, bool NEED_ARG, int NC = 1>
 __device__ __forceinline__ void fold_item(const TeamArgs& A, const ItemPos& q, uint32_t tag,
                                           int lane, int wv, int first, int rot = 0) {
   const int order = (wv + kWaves - first) % kWaves;
   for (int rr = duty_index(q.s, rot, A.S) + order * A.S; rr <= q.n; rr += kWaves * A.S)
-    fold_row<D, NEED_SUM, NEED_ARG, NC>(A, q.set, rr, q.b, q.k, q.sub, tag, lane);
+    fold_row<D, NEED_ARG, NC>(A, q.set, rr, q.b, q.k, q.sub, tag, lane);
 }
 
 // ---- 5. normalisers L = hi + lo (the duty wave; a barrier follows): lanes 2r and 2r + 1 wait for
 // row r's hi and lo; lane 2r forms a_r = (o_r - hi_r) - lo_r, o_r the offset of the row's
 // exponents, and, for a drafter row, the constants of its min-sum to LDS. Differences of the
 // a_r are taken part by part, so that they lose nothing to a large hi.
-// o_r = 0, except after a retry (AGAIN, every normaliser final), where it is the slice's offset
+// o_r = A.o, except after a retry (AGAIN, every normaliser final), where it is the slice's offset
 // with kept e_v and rint(hi_r) in the wide form.
-// KEPT (6'): G = 2^(a_t - a_d) and F = 2^(a_d). Else (6): exponent addend nw = -(a_t - a_d), or
+// KEPT (6'): G = 2^(a_t - a_d) and F = 2^(a_d). Else (6): exponent addend nw = -A.o - (a_t - a_d), or
 // the difference itself in the wide form, and F = 2^(a_t).
 // A row with no finite logit folds to hi = -inf, lo = NaN, so its a is NaN: it has no
 // distribution, and F is NaN whenever a_t or a_d is, which makes that drafter's alpha NaN in
@@ -646,7 +569,7 @@ __device__ __forceinline__ void await_norms(const TeamArgs& A, const ItemPos& q,
     sh.form = AGAIN ? kWide : (uint32_t)retry;
   }
   const float lo = dpp_f<0xB1>(h);  // lane 2r: the lo of row r, from lane 2r + 1
-  float o = 0.0f;
+  float o = A.o;
   if (AGAIN && row) {
     if (KEPT) {
       o = sh.o[lane >> 1];
@@ -666,7 +589,7 @@ __device__ __forceinline__ void await_norms(const TeamArgs& A, const ItemPos& q,
       sh.G[d] = __builtin_amdgcn_exp2f(diff);
       sh.F[d] = undefined ? NAN : exp2_split(x, lo);
     } else {
-      sh.nw[d] = -diff;
+      sh.nw[d] = -A.o - diff;
       if (AGAIN) sh.dl[d] = diff;
       sh.F[d] = undefined ? NAN : exp2_split(xt, lot);
     }
@@ -716,7 +639,7 @@ __device__ __forceinline__ void retry_item(const TeamArgs& A, const ItemPos& q, 
     m = fkey_inv(row16_max(k));
     if (gl == 0 && gi <= q.n) {
       const float o = exp_offset_of(m, A.c);
-      if (KEPT) sh.o[gi] = mine ? o : 0.0f;
+      if (KEPT) sh.o[gi] = mine ? o : A.o;
       sh.no[gi] = -exp_offset(o);
     }
   }
@@ -771,9 +694,9 @@ __device__ __forceinline__ void thread_minsums_kept(const ItemPos& q,
 
 // ---- 6. per-thread min-sums, from the logits again: with u_v = z_t,v c - o_t and
 // w_v = z_d,v c - o_d, p_v = 2^(u_v + a_t) and q_v = 2^(w_v + a_d), so
-// min(p_v, q_v) = 2^(a_t) 2^min(u_v, w_v - (a_t - a_d)), and in the plain form (both o = 0)
+// min(p_v, q_v) = 2^(a_t) 2^min(u_v, w_v - (a_t - a_d)), and in the plain form (both o = A.o)
 // w_v - (a_t - a_d) is one fma z_d,v c + nw_d; one fma, one min, one exp2 and one add per
-// drafter logit. The factor 2^(a_t) is applied to the group sum. Identical rows give nw_d = 0,
+// drafter logit. The factor 2^(a_t) is applied to the group sum. Identical rows give nw_d = -o,
 // so both operands agree bitwise ----
 template <int DT, int D, bool WIDE, typename L>
 __device__ __forceinline__ void thread_minsums_form(const TeamArgs& A, const ItemPos& q,
@@ -783,9 +706,9 @@ __device__ __forceinline__ void thread_minsums_form(const TeamArgs& A, const Ite
   float u[E];
   launder(raw[0]);
   Vec<DT>::unpack(raw[0], u);
-  const float nt = WIDE ? sh.no[0] : 0.0f;
+  const float nt = WIDE ? sh.no[0] : -A.o;
 #pragma unroll
-  for (int e = 0; e < E; ++e) u[e] = WIDE ? fmaf(u[e], A.c, nt) : u[e] * A.c;
+  for (int e = 0; e < E; ++e) u[e] = fmaf(u[e], A.c, nt);
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     if (d >= q.n) continue;
@@ -943,11 +866,14 @@ __device__ __forceinline__ void finish(const TeamArgs& A, uint32_t tag, bool cou
 // on every large workload than three workgroups with three buffers.
 // SINGLE (alpha kernels only): every team has exactly one item, so nothing is pipelined, the
 // e_v stay in registers and drafters at a constant distance are addressed without the table.
-template <int DT, int D, bool NEED_SUM, bool NEED_ARG, bool SINGLE>
-__global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
+// With an argmax as well the pipelined kernel runs 3 workgroups per CU: held to the 128 registers of
+// a fourth it spills 140 bytes and runs 58 us instead of 45 (13 queries x 5 drafters x 7 positions x
+// 50257 fp16 logits).
+template <int DT, int D, bool NEED_ARG, bool SINGLE>
+__global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team_kernel(TeamArgs A) {
   using Raw = typename Vec<DT>::Raw;
   constexpr int RM = D + 1;
-  __shared__ TeamLds<D, NEED_SUM, NEED_ARG> sh;
+  __shared__ TeamLds<D, NEED_ARG> sh;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int gi = t >> 4, gl = t & 15;  // 16-lane group gi reduces row gi; gl: lane in it
   const int S = A.S;
@@ -955,7 +881,7 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
   // is loaded just before its first use, one scalar-cache round trip apiece); the pipelined
   // alpha kernel, whose first loads are a small part of its run, loads them at first use
   // instead (0.6% faster there: fewer scalar registers held across its loop)
-  if constexpr (SINGLE || !NEED_SUM) {
+  if constexpr (SINGLE) {
     asm volatile("" ::"s"(A.N), "s"(A.K), "s"(A.nsub), "s"(A.S), "s"(A.items), "s"(A.teams),
                  "s"(A.uni), "s"(A.divS.m), "s"(A.divS.s1), "s"(A.divS.s2), "s"(A.divK.m),
                  "s"(A.divK.s1), "s"(A.divK.s2), "s"(A.V), "s"(A.dd), "s"(A.base0),
@@ -969,16 +895,15 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
   // workgroups a CU holds at once (w, w + CUs, ...) take different slices also when S divides
   // the number of CUs (8% on 64 stacked fp32 tiny chains, S = 32; no change where it does not)
   int slot = (int)blockIdx.x - T * S;
-  if constexpr (NEED_SUM && !SINGLE) {
+  if constexpr (!SINGLE) {
     slot += T - (int)fdiv((uint32_t)T, A.divS) * S;  // + T mod S
     if (slot >= S) slot -= S;
   }
   const uint32_t nsets = fdiv((uint32_t)A.items, A.divS);
-  constexpr int kStatic = NEED_SUM ? 3 : 2;  // items per team with a fixed row set
-  // slot 0 folds row 0 of every item, so it waits for the whole team each item: it can never
-  // be more than one item ahead of any member, which keeps a ring of 4 mailbox words safe
+  // slot 0 is its team's leader: it waits for the normalisers of each item, which need the whole
+  // team, so it can never be more than one item ahead of any member, which keeps a ring of 4
+  // mailbox words safe
   const bool leader = slot == 0;
-  const bool dynamic = kStatic * teams < (int)nsets;  // else no team has more than its fixed sets
   uint32_t tag = 0;  // the call's tag: read once the first loads are in flight
   uint64_t* mbox = A.mbox + (size_t)T * 4;
   if (!(SINGLE && A.uni) && t < kMaxRows) {
@@ -988,202 +913,158 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_kernel(TeamArgs A) {
   }
   __syncthreads();
 
-  // the row set of the team's item j < kStatic
-  auto fixed_set = [&](int j) { return min((uint32_t)(T + j * teams), nsets); };
-  // leader: claim the row set of the team's item j >= kStatic and post it (the counter starts
-  // past every team's fixed sets, so a set is never claimed twice, and once a team's next item
-  // has none every later claim has none either)
-  auto claim = [&](int j) __attribute__((always_inline)) {
-    if (!dynamic || !leader || t != 0) return;
-    const uint32_t v = (uint32_t)(kStatic * teams) +
-                       __hip_atomic_fetch_add(A.next_set, 1u, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT);
-    put_word(mbox + (j & 3), mbox_word(min(v, nsets), j, tag));
-  };
-  // thread 0: the row set of the team's item j >= kStatic (nsets: none left) into LDS, so that
-  // all waves of the workgroup take the same one after the next barrier
-  auto post_set = [&](int j) __attribute__((always_inline)) {
-    if (t == 0) sh.next = dynamic ? await_mbox(mbox + (j & 3), j, tag, A, nsets) : nsets;
-  };
   // first slot of the row or alpha fold duties of row set `set` (several items per workgroup):
   // (set (D + 1) + extra) mod S, so consecutive items use different members, and the alpha
-  // folds of an item start where its row folds end. (The argmax-only kernel keeps row 0 on
-  // the leader, which bounds how far the leader's claims run ahead of its team; in the alpha
-  // kernels every member waits for the normalisers of each item, which bounds it there.)
+  // folds of an item start where its row folds end.
   auto rotation = [&](uint32_t s, int extra) __attribute__((always_inline)) -> int {
     const uint32_t x = s * (uint32_t)RM + (uint32_t)extra;
     return (int)(x - fdiv(x, A.divS) * (uint32_t)S);
   };
 
-  if constexpr (!NEED_SUM) {
-    // argmax only: max stage, publish, fold
-    Raw nxt[RM];
-    uint32_t set = (uint32_t)T, next = fixed_set(1);
-    fetch_item<DT, D>(A, item_pos(A, set, slot, D), true, sh, nxt);
-    tag = call_tag(A.epoch);  // first needed once the first loads are in flight
-    for (int j = 0; set < nsets; ++j) {
-      const ItemPos q = item_pos(A, set, slot, D);
-      __builtin_amdgcn_s_setprio(kCritPrio);
-      mask_tail<DT, D>(A, q, nxt);
-      thread_stats<DT, D, false, NEED_ARG, false>(A, q, nxt, sh, sh, t);
-      if (j >= 1) post_set(j + 1);
-      claim(j + 2);
-      __syncthreads();
-      if (j >= 1) next = sh.next;
-      if (next < nsets) fetch_item<DT, D>(A, item_pos(A, next, slot, D), true, sh, nxt);
-      if (wv * 4 <= q.n) publish_stats<false, NEED_ARG>(A, q, tag, RM, sh, gi, gl);
-      fold_item<D, false, NEED_ARG>(A, q, tag, lane, wv, kDutyWave);
-      __builtin_amdgcn_s_setprio(0);
-      __syncthreads();  // the LDS rows are free for the next item
-      set = next;
-    }
-    finish(A, tag, leader, teams, sh, t);
-  } else {
-    // statistics of item q from raw, published
-    auto stats = [&](const ItemPos& q, Raw (&raw)[RM]) __attribute__((always_inline)) {
-      __builtin_amdgcn_s_setprio(kCritPrio);
-      mask_tail<DT, D>(A, q, raw);
-      thread_stats<DT, D, true, NEED_ARG, false>(A, q, raw, sh, sh, t);
-      __syncthreads();
-      if (wv * 4 <= q.n)  // this wave holds the group of a row
-        publish_stats<true, NEED_ARG>(A, q, tag, RM, sh, gi, gl);
-      __builtin_amdgcn_s_setprio(0);
-    };
-    // the item's slice partials to the workspace (after a barrier), as tagged words
-    auto store_partials = [&](const ItemPos& q) __attribute__((always_inline)) {
-      if (wv * 4 < q.n) {
-        float v[16];
-        const int d = min(gi, q.n - 1);
-        group_read(&sh.xp[d][0], gl, v);
-        const float y = row16_sum(sum16(v));
-        if (gl == 0 && gi < q.n)
-          put_word(A.part + ((int64_t)q.g * A.N + q.sub * D + gi) * S + q.s,
-                   word_of(y * sh.F[gi], tag | sh.taint));
-      }
-    };
-
-    // Several items per workgroup: the row sets of one (query, position) group follow each
-    // other in a team when there are groups enough to keep every team busy, so the target's
-    // slice, the same for all of them, is re-read from this XCD's L2 rather than from HBM. A
-    // team's items come in blocks (a group's nsub row sets, else single row sets): its first
-    // kB blocks are blocks T, T + teams, ... (at least three items, to fill the pipeline), and
-    // later ones are claimed from the device-wide counter three items ahead, by the leader,
-    // and posted in the team's mailbox ring.
-    const bool blocked = !SINGLE && A.nsub > 1 && nsets >= 4u * (uint32_t)teams * (uint32_t)A.nsub;
-    const uint32_t bsz = blocked ? (uint32_t)A.nsub : 1u;
-    const uint32_t nblocks = blocked ? fdiv(nsets, A.divNsub) : nsets;
-    const int kB = blocked ? (int)((3u + bsz - 1u) / bsz) : 3;
-    const bool dyn = kB * teams < (int)nblocks;  // else no team has more than its fixed blocks
-    int nblk = 0;  // blocks given to this team so far (the same count in every member)
-    auto block_first = [&](uint32_t bl) { return bl < nblocks ? bl * bsz : nsets; };
-    // the row set after s (nsets: none), or kClaim when it starts a block that is to be claimed
-    constexpr uint32_t kClaim = 0xFFFFFFFFu;
-    auto successor = [&](uint32_t s) __attribute__((always_inline)) -> uint32_t {
-      if (s >= nsets) return nsets;
-      if (blocked && fdiv(s + 1u, A.divNsub) * bsz != s + 1u) return s + 1u;  // same group
-      if (nblk < kB) return block_first((uint32_t)(T + (nblk++) * teams));
-      return dyn ? kClaim : nsets;
-    };
-
-    Raw R0[RM], R1[RM];
-    uint32_t set = SINGLE ? (uint32_t)T : block_first((uint32_t)T);
-    nblk = 1;
-    const ItemPos q0 = item_pos(A, set, slot, D);
-    fetch_item<DT, D, SINGLE>(A, q0, true, sh, R0);
-    if constexpr (SINGLE) {
-      // one item per workgroup: nothing to overlap, so its e_v stay in registers
-      tag = call_tag(A.epoch);  // first needed once the first loads are in flight
-      const ItemPos& q = q0;
-      float x[RM][Vec<DT>::kElems];
-      __builtin_amdgcn_s_setprio(kCritPrio);
-      mask_tail<DT, D>(A, q, R0);
-      thread_stats<DT, D, true, NEED_ARG, true>(A, q, R0, x, sh, t);
-      __syncthreads();
-      if (wv * 4 <= q.n) publish_stats<true, NEED_ARG>(A, q, tag, RM, sh, gi, gl);
-      fold_item<D, true, NEED_ARG, kNormCopies>(A, q, tag, lane, wv, 0);
-      __builtin_amdgcn_s_setprio(0);
-      // with one item per workgroup the leader counts its team once it has folded row 0 (every
-      // member has published, so has read the tag), not at its end: the count's round trip
-      // then overlaps the normaliser wait instead of following the learner step or the alpha
-      // folds. (The fold duties start at wave 0, whose thread 0 counts.)
-      if (leader && t == 0) count_team(A, tag, teams);
-      if (wv == 0) await_norms<D, true, false>(A, q, tag, sh, lane);
-      __syncthreads();
-      const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
-      if (form) retry_item<DT, D, true, kNormCopies>(A, q, form, tag, x, sh, t, 0, 0);
-      thread_minsums_kept<DT, D>(q, x, sh, t);
-      __syncthreads();
-      store_partials(q);
-      fold_alpha<D>(A, q, tag, lane, wv);
-      if (A.learn)
-        for (int b = blockIdx.x; b < A.B; b += gridDim.x) learn_query(A, tag, b, sh, t);
-      finish(A, tag, false, teams, sh, t);
-      return;
-    }
-    uint32_t set1 = successor(set);
-    uint32_t set2 = successor(set1);  // items 0-2 lie in fixed blocks: never kClaim
-    fetch_item<DT, D>(A, item_pos(A, min(set1, nsets - 1), slot, D), set1 < nsets, sh,
-                      R1);
-    tag = call_tag(A.epoch);  // first needed once the first loads are in flight
-    stats(q0, R0);
-    // the first item's group reductions read every column of the LDS rows that the next
-    // item's per-thread statistics overwrite, and nothing else in the first iteration waits
-    // for the whole workgroup before those writes (later items are kept apart by the
-    // barriers around the min-sums); after it every wave has published its rows
+  // statistics of item q from raw, published
+  auto stats = [&](const ItemPos& q, Raw (&raw)[RM]) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(kCritPrio);
+    mask_tail<DT, D>(A, q, raw);
+    thread_stats<DT, D, NEED_ARG, false>(A, q, raw, sh, sh, t);
     __syncthreads();
-
-    uint32_t pset = nsets;  // the team's previous item, whose alpha is still to be folded
-    // iteration j: rc holds item j (statistics published) and then receives item j + 2, rn
-    // holds item j + 1 (loaded). Returns false once the team has no item j + 1.
-    auto iter = [&](int j, Raw (&rc)[RM], Raw (&rn)[RM])
-                    __attribute__((always_inline)) -> bool {
-      const ItemPos q = item_pos(A, set, slot, D);
-      // the leader's claim of item j + 3 goes out before the fold and is posted after it, so
-      // waiting for its result waits for nothing else; the duty wave, which folds, claims
-      // (the argmax-only kernel, whose folds are short, claims on thread 0)
-      const uint32_t set3 = successor(set2);  // item j + 3, unless it is to be claimed
-      const bool claiming = set3 == kClaim && leader && wv == kDutyWave && lane == 0;
-      uint32_t cv = 0;
-      if (claiming)
-        cv = __hip_atomic_fetch_add(A.next_set, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_s_setprio(kFoldPrio);
-      fold_item<D, true, NEED_ARG>(A, q, tag, lane, wv, kDutyWave, rotation(set, 0));
-      __builtin_amdgcn_s_setprio(0);
-      if (claiming)
-        put_word(mbox + ((j + 3) & 3),
-                 mbox_word(block_first((uint32_t)(kB * teams) + cv), j + 3, tag));
-      if (set1 < nsets) stats(item_pos(A, set1, slot, D), rn);
-      else __syncthreads();  // the previous item's constants in LDS are no longer read
-      if (set3 == kClaim && t == 0) sh.next = await_mbox(mbox + ((j + 3) & 3), j + 3, tag, A, nsets);
-      if (wv == kDutyWave) await_norms<D, false, false>(A, q, tag, sh, lane);
-      __syncthreads();
-      const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
-      if (form)
-        retry_item<DT, D, false, 1>(A, q, form, tag, sh, sh, t, kDutyWave, rotation(set, 0));
-      thread_minsums<DT, D>(A, q, rc, sh, t);
-      __syncthreads();
-      store_partials(q);
-      fetch_item<DT, D>(A, item_pos(A, min(set2, nsets - 1), slot, D), set2 < nsets, sh, rc);
-      // alpha of the previous item, whose partials were stored an iteration ago; its polls
-      // overlap the loads just issued (1.4% faster than folding it before the normaliser wait)
-      if (pset < nsets) fold_alpha<D>(A, item_pos(A, pset, slot, D), tag, lane, wv, rotation(pset, RM));
-      if (set1 >= nsets) return false;
-      pset = set;
-      set = set1;
-      set1 = set2;
-      set2 = set3 == kClaim ? sh.next : set3;
-      return true;
-    };
-    // unrolled by two so that the register buffers alternate without copies
-    for (int j = 0;; j += 2) {
-      if (!iter(j, R0, R1)) break;
-      if (!iter(j + 1, R1, R0)) break;
+    if (wv * 4 <= q.n)  // this wave holds the group of a row
+      publish_stats<NEED_ARG>(A, q, tag, RM, sh, gi, gl);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  // the item's slice partials to the workspace (after a barrier), as tagged words
+  auto store_partials = [&](const ItemPos& q) __attribute__((always_inline)) {
+    if (wv * 4 < q.n) {
+      float v[16];
+      const int d = min(gi, q.n - 1);
+      group_read(&sh.xp[d][0], gl, v);
+      const float y = row16_sum(sum16(v));
+      if (gl == 0 && gi < q.n)
+        put_word(A.part + ((int64_t)q.g * A.N + q.sub * D + gi) * S + q.s,
+                 word_of(y * sh.F[gi], tag | sh.taint));
     }
-    fold_alpha<D>(A, item_pos(A, set, slot, D), tag, lane, wv, rotation(set, RM));
+  };
+
+  // Several items per workgroup: the row sets of one (query, position) group follow each
+  // other in a team when there are groups enough to keep every team busy, so the target's
+  // slice, the same for all of them, is re-read from this XCD's L2 rather than from HBM. A
+  // team's items come in blocks (a group's nsub row sets, else single row sets): its first
+  // kB blocks are blocks T, T + teams, ... (at least three items, to fill the pipeline), and
+  // later ones are claimed from the device-wide counter three items ahead, by the leader,
+  // and posted in the team's mailbox ring.
+  const bool blocked = !SINGLE && A.nsub > 1 && nsets >= 4u * (uint32_t)teams * (uint32_t)A.nsub;
+  const uint32_t bsz = blocked ? (uint32_t)A.nsub : 1u;
+  const uint32_t nblocks = blocked ? fdiv(nsets, A.divNsub) : nsets;
+  const int kB = blocked ? (int)((3u + bsz - 1u) / bsz) : 3;
+  const bool dyn = kB * teams < (int)nblocks;  // else no team has more than its fixed blocks
+  int nblk = 0;  // blocks given to this team so far (the same count in every member)
+  auto block_first = [&](uint32_t bl) { return bl < nblocks ? bl * bsz : nsets; };
+  // the row set after s (nsets: none), or kClaim when it starts a block that is to be claimed
+  constexpr uint32_t kClaim = 0xFFFFFFFFu;
+  auto successor = [&](uint32_t s) __attribute__((always_inline)) -> uint32_t {
+    if (s >= nsets) return nsets;
+    if (blocked && fdiv(s + 1u, A.divNsub) * bsz != s + 1u) return s + 1u;  // same group
+    if (nblk < kB) return block_first((uint32_t)(T + (nblk++) * teams));
+    return dyn ? kClaim : nsets;
+  };
+
+  Raw R0[RM], R1[RM];
+  uint32_t set = SINGLE ? (uint32_t)T : block_first((uint32_t)T);
+  nblk = 1;
+  const ItemPos q0 = item_pos(A, set, slot, D);
+  fetch_item<DT, D, SINGLE>(A, q0, true, sh, R0);
+  if constexpr (SINGLE) {
+    // one item per workgroup: nothing to overlap, so its e_v stay in registers
+    tag = call_tag(A.epoch);  // first needed once the first loads are in flight
+    const ItemPos& q = q0;
+    float x[RM][Vec<DT>::kElems];
+    __builtin_amdgcn_s_setprio(kCritPrio);
+    mask_tail<DT, D>(A, q, R0);
+    thread_stats<DT, D, NEED_ARG, true>(A, q, R0, x, sh, t);
+    __syncthreads();
+    if (wv * 4 <= q.n) publish_stats<NEED_ARG>(A, q, tag, RM, sh, gi, gl);
+    fold_item<D, NEED_ARG, kNormCopies>(A, q, tag, lane, wv, 0);
+    __builtin_amdgcn_s_setprio(0);
+    // with one item per workgroup the leader counts its team once it has folded row 0 (every
+    // member has published, so has read the tag), not at its end: the count's round trip
+    // then overlaps the normaliser wait instead of following the learner step or the alpha
+    // folds. (The fold duties start at wave 0, whose thread 0 counts.)
+    if (leader && t == 0) count_team(A, tag, teams);
+    if (wv == 0) await_norms<D, true, false>(A, q, tag, sh, lane);
+    __syncthreads();
+    const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
+    if (form) retry_item<DT, D, true, kNormCopies>(A, q, form, tag, x, sh, t, 0, 0);
+    thread_minsums_kept<DT, D>(q, x, sh, t);
+    __syncthreads();
+    store_partials(q);
+    fold_alpha<D>(A, q, tag, lane, wv);
     if (A.learn)
       for (int b = blockIdx.x; b < A.B; b += gridDim.x) learn_query(A, tag, b, sh, t);
-    finish(A, tag, leader, teams, sh, t);
+    finish(A, tag, false, teams, sh, t);
+    return;
   }
+  uint32_t set1 = successor(set);
+  uint32_t set2 = successor(set1);  // items 0-2 lie in fixed blocks: never kClaim
+  fetch_item<DT, D>(A, item_pos(A, min(set1, nsets - 1), slot, D), set1 < nsets, sh,
+                    R1);
+  tag = call_tag(A.epoch);  // first needed once the first loads are in flight
+  stats(q0, R0);
+  // the first item's group reductions read every column of the LDS rows that the next
+  // item's per-thread statistics overwrite, and nothing else in the first iteration waits
+  // for the whole workgroup before those writes (later items are kept apart by the
+  // barriers around the min-sums); after it every wave has published its rows
+  __syncthreads();
+
+  uint32_t pset = nsets;  // the team's previous item, whose alpha is still to be folded
+  // iteration j: rc holds item j (statistics published) and then receives item j + 2, rn
+  // holds item j + 1 (loaded). Returns false once the team has no item j + 1.
+  auto iter = [&](int j, Raw (&rc)[RM], Raw (&rn)[RM])
+                  __attribute__((always_inline)) -> bool {
+    const ItemPos q = item_pos(A, set, slot, D);
+    // the leader's claim of item j + 3 goes out before the fold and is posted after it, so
+    // waiting for its result waits for nothing else; the duty wave, which folds, claims
+    // (the argmax-only kernel, whose folds are short, claims on thread 0)
+    const uint32_t set3 = successor(set2);  // item j + 3, unless it is to be claimed
+    const bool claiming = set3 == kClaim && leader && wv == kDutyWave && lane == 0;
+    uint32_t cv = 0;
+    if (claiming)
+      cv = __hip_atomic_fetch_add(A.next_set, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_setprio(kFoldPrio);
+    fold_item<D, NEED_ARG>(A, q, tag, lane, wv, kDutyWave, rotation(set, 0));
+    __builtin_amdgcn_s_setprio(0);
+    if (claiming)
+      put_word(mbox + ((j + 3) & 3),
+               mbox_word(block_first((uint32_t)(kB * teams) + cv), j + 3, tag));
+    if (set1 < nsets) stats(item_pos(A, set1, slot, D), rn);
+    else __syncthreads();  // the previous item's constants in LDS are no longer read
+    if (set3 == kClaim && t == 0) sh.next = await_mbox(mbox + ((j + 3) & 3), j + 3, tag, A, nsets);
+    if (wv == kDutyWave) await_norms<D, false, false>(A, q, tag, sh, lane);
+    __syncthreads();
+    const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
+    if (form)
+      retry_item<DT, D, false, 1>(A, q, form, tag, sh, sh, t, kDutyWave, rotation(set, 0));
+    thread_minsums<DT, D>(A, q, rc, sh, t);
+    __syncthreads();
+    store_partials(q);
+    fetch_item<DT, D>(A, item_pos(A, min(set2, nsets - 1), slot, D), set2 < nsets, sh, rc);
+    // alpha of the previous item, whose partials were stored an iteration ago; its polls
+    // overlap the loads just issued (1.4% faster than folding it before the normaliser wait)
+    if (pset < nsets) fold_alpha<D>(A, item_pos(A, pset, slot, D), tag, lane, wv, rotation(pset, RM));
+    if (set1 >= nsets) return false;
+    pset = set;
+    set = set1;
+    set1 = set2;
+    set2 = set3 == kClaim ? sh.next : set3;
+    return true;
+  };
+  // unrolled by two so that the register buffers alternate without copies
+  for (int j = 0;; j += 2) {
+    if (!iter(j, R0, R1)) break;
+    if (!iter(j + 1, R1, R0)) break;
+  }
+  fold_alpha<D>(A, item_pos(A, set, slot, D), tag, lane, wv, rotation(set, RM));
+  if (A.learn)
+    for (int b = blockIdx.x; b < A.B; b += gridDim.x) learn_query(A, tag, b, sh, t);
+  finish(A, tag, leader, teams, sh, t);
 }
 
 // ---- host side -------------------------------------------------------------------------------
@@ -1198,7 +1079,7 @@ std::atomic<uint32_t> g_wait_polls{kDefaultPolls};
 uint32_t wait_polls() { return g_wait_polls.load(std::memory_order_relaxed); }
 
 // Workgroups of the team kernel the current device holds at once.
-template <int DT, int D, bool NS, bool NA, bool SG>
+template <int DT, int D, bool NA, bool SG>
 int capacity_t() {
   static std::atomic<int> cached[64];  // per device; 0 = not yet known
   int dev = 0;
@@ -1206,7 +1087,7 @@ int capacity_t() {
   int v = cached[dev].load(std::memory_order_relaxed);
   if (v > 0) return v;
   int per_cu = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, hs_team_kernel<DT, D, NS, NA, SG>,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, hs_team_kernel<DT, D, NA, SG>,
                                                    kThreads, 0) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
@@ -1218,62 +1099,59 @@ int capacity_t() {
 // Runs the team kernel with as many teams as the device holds at once (no more than there are
 // row sets or mailbox rings); the single-item kernel when that covers every row set.
 // *learned: whether the launch runs the learner step itself (its LDS fits in the team's).
-template <int DT, int D, bool NS, bool NA>
+template <int DT, int D, bool NA>
 int launch_t(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* learned) {
   const int64_t sets = g.items / g.S;
-  const bool single = NS && capacity_t<DT, D, NS, NA, NS>() / g.S >= sets;
+  const bool single = capacity_t<DT, D, NA, true>() / g.S >= sets;
   const int64_t teams =
       single ? sets
-             : std::min<int64_t>({capacity_t<DT, D, NS, NA, false>() / g.S, sets,
+             : std::min<int64_t>({capacity_t<DT, D, NA, false>() / g.S, sets,
                                   (int64_t)kMaxTeams});
   if (teams <= 0) return HS_ERR_LIMIT;
   const int64_t P = teams * g.S;
-  if (A.learn) {  // only the alpha kernels carry the learner (it would cost the argmax-only
-                  // kernels a workgroup per CU in registers)
+  if (A.learn) {
     const size_t need = sizeof(double) * (size_t)tail_lds_doubles(A.tail) +
                         sizeof(float) * (size_t)g.N * g.K;
-    if (!NS || need > sizeof(TeamLds<D, NS, NA>)) A.learn = 0;
+    if (need > sizeof(TeamLds<D, NA>)) A.learn = 0;
   }
   *learned = A.learn != 0;
   A.teams = (int)teams;
-  if (single) hs_team_kernel<DT, D, NS, NA, NS><<<(unsigned)P, kThreads, 0, stream>>>(A);
-  else hs_team_kernel<DT, D, NS, NA, false><<<(unsigned)P, kThreads, 0, stream>>>(A);
+  if (single) hs_team_kernel<DT, D, NA, true><<<(unsigned)P, kThreads, 0, stream>>>(A);
+  else hs_team_kernel<DT, D, NA, false><<<(unsigned)P, kThreads, 0, stream>>>(A);
   return HS_OK;
 }
 
-// Calls F<DT, D, NS, NA>::run(args...) for the geometry and mode.
-template <template <int, int, bool, bool> class F, int DT, int D, typename... Args>
-int by_mode(bool ns, bool na, Args&&... args) {
-  if (ns && na) return F<DT, D, true, true>::run(args...);
-  if (ns) return F<DT, D, true, false>::run(args...);
-  return F<DT, D, false, true>::run(args...);
+// Calls F<DT, D, NA>::run(args...) for the geometry and mode.
+template <template <int, int, bool> class F, int DT, int D, typename... Args>
+int by_mode(bool na, Args&&... args) {
+  return na ? F<DT, D, true>::run(args...) : F<DT, D, false>::run(args...);
 }
-template <template <int, int, bool, bool> class F, int DT, typename... Args>
-int by_set(int D, bool ns, bool na, Args&&... args) {
+template <template <int, int, bool> class F, int DT, typename... Args>
+int by_set(int D, bool na, Args&&... args) {
   switch (D) {
-    case 1: return by_mode<F, DT, 1>(ns, na, args...);
-    case 2: return by_mode<F, DT, 2>(ns, na, args...);
-    case 4: return by_mode<F, DT, 4>(ns, na, args...);
-    default: return by_mode<F, DT, kMaxSetDrafters>(ns, na, args...);
+    case 1: return by_mode<F, DT, 1>(na, args...);
+    case 2: return by_mode<F, DT, 2>(na, args...);
+    case 4: return by_mode<F, DT, 4>(na, args...);
+    default: return by_mode<F, DT, kMaxSetDrafters>(na, args...);
   }
 }
-template <template <int, int, bool, bool> class F, typename... Args>
-int dispatch(const TeamGeom& g, bool ns, bool na, Args&&... args) {
-  if (g.dtype == HS_F32) return by_set<F, HS_F32>(g.D, ns, na, args...);
-  if (g.dtype == HS_F16) return by_set<F, HS_F16>(g.D, ns, na, args...);
-  return by_set<F, HS_BF16>(g.D, ns, na, args...);
+template <template <int, int, bool> class F, typename... Args>
+int dispatch(const TeamGeom& g, bool na, Args&&... args) {
+  if (g.dtype == HS_F32) return by_set<F, HS_F32>(g.D, na, args...);
+  if (g.dtype == HS_F16) return by_set<F, HS_F16>(g.D, na, args...);
+  return by_set<F, HS_BF16>(g.D, na, args...);
 }
 
-template <int DT, int D, bool NS, bool NA>
+template <int DT, int D, bool NA>
 struct Capacity {  // the smaller of the two kernels' (a team must fit in either)
   static int run() {
-    return std::min(capacity_t<DT, D, NS, NA, false>(), capacity_t<DT, D, NS, NA, NS>());
+    return std::min(capacity_t<DT, D, NA, false>(), capacity_t<DT, D, NA, true>());
   }
 };
-template <int DT, int D, bool NS, bool NA>
+template <int DT, int D, bool NA>
 struct Launch {
   static int run(const TeamArgs& A, const TeamGeom& g, hipStream_t s, bool* learned) {
-    return launch_t<DT, D, NS, NA>(A, g, s, learned);
+    return launch_t<DT, D, NA>(A, g, s, learned);
   }
 };
 
@@ -1283,8 +1161,8 @@ void set_wait_polls(int polls) {
   g_wait_polls.store(polls < 0 ? kDefaultPolls : (uint32_t)polls, std::memory_order_relaxed);
 }
 
-int team_capacity(const TeamGeom& g, bool need_sum, bool need_arg) {
-  return dispatch<Capacity>(g, need_sum, need_arg);
+int team_capacity(const TeamGeom& g, bool need_arg) {
+  return dispatch<Capacity>(g, need_arg);
 }
 
 int launch_round(const TeamGeom& g, const RowTable& rows, float c, bool need_sum, bool need_arg,
@@ -1292,6 +1170,19 @@ int launch_round(const TeamGeom& g, const RowTable& rows, float c, bool need_sum
                  const TailArgs* tail, hipStream_t stream) {
   const TeamWs L = team_ws(g);
   TeamArgs A{};
+  A.epoch = reinterpret_cast<uint32_t*>(ws + L.epoch);
+  A.fail = reinterpret_cast<uint64_t*>(ws + L.epoch + 8);
+  // a learner step of its own, told where to see whether the evaluation failed
+  auto tail_after = [&]() -> int {
+    TailArgs a = *tail;
+    a.round_epoch = A.epoch;
+    a.round_fail = A.fail;
+    return launch_tail(a, stream);
+  };
+  if (!need_sum) {
+    const int rc = launch_argmax(g, rows, agree, argmax_t, argmax_d, wait_polls(), ws, stream);
+    return rc || !tail ? rc : tail_after();
+  }
   A.rows = rows;
   A.base0 = rows.ptr[0];
   A.base1 = rows.ptr[1];
@@ -1321,16 +1212,20 @@ int launch_round(const TeamGeom& g, const RowTable& rows, float c, bool need_sum
   A.V = g.V;
   A.nvec = g.nvec;
   A.c = c;
-  A.epoch = reinterpret_cast<uint32_t*>(ws + L.epoch);
-  A.fail = reinterpret_cast<uint64_t*>(ws + L.epoch + 8);
+  // About 5.5 logits above 0, as an integer power of two: an exponent is rounded at 2^-24 of its own
+  // size, and this puts those of the heavy tokens of a head (logits of 0 to 20) nearest to 0.
+  // alpha's error against 64 bits (2-norm, simulated rounding, heads of 50k to 76k tokens): 1.5e-7,
+  // 2.2e-7 and 3.3e-7 at T = 1, 0.7 and 0.5; with offset 0 1.8e-7, 2.2e-7 and 5.2e-7, with offset
+  // 16 2.0e-7, 2.0e-7 and 3.3e-7, and with each slice's maximum 1.7e-7, 2.3e-7 and 4.7e-7.
+  A.o = std::nearbyint(std::min(5.5f * c, 48.0f));
   A.polls = wait_polls();
   A.next_set = reinterpret_cast<uint32_t*>(ws + L.epoch + 16);
   A.finished = reinterpret_cast<uint64_t*>(ws + L.epoch + 24);
   A.mbox = reinterpret_cast<uint64_t*>(ws + L.epoch + 64);
   A.stat = reinterpret_cast<uint64_t*>(ws + L.stat);
   A.norm = reinterpret_cast<uint64_t*>(ws + L.norm);
-  A.part = need_sum ? reinterpret_cast<uint64_t*>(ws + L.part) : nullptr;
-  A.alpha = need_sum ? alpha : nullptr;
+  A.part = reinterpret_cast<uint64_t*>(ws + L.part);
+  A.alpha = alpha;
   A.argmax_t = argmax_t;
   A.argmax_d = argmax_d;
   A.agree = agree;
@@ -1342,15 +1237,10 @@ int launch_round(const TeamGeom& g, const RowTable& rows, float c, bool need_sum
     A.tail = *tail;
   }
   bool learned = false;
-  int rc = dispatch<Launch>(g, need_sum, need_arg, A, g, stream, &learned);
+  int rc = dispatch<Launch>(g, need_arg, A, g, stream, &learned);
   if (rc) return rc;
   if (hipGetLastError() != hipSuccess) return HS_ERR_HIP;
-  if (tail && !learned) {  // a launch of its own, told where to see whether this one failed
-    A.tail.round_epoch = A.epoch;
-    A.tail.round_fail = A.fail;
-    return launch_tail(A.tail, stream);
-  }
-  return HS_OK;
+  return tail && !learned ? tail_after() : HS_OK;
 }
 
 }  // namespace hs

@@ -1,0 +1,93 @@
+"""The argmax kernel (greedy mode without alpha) and the alpha kernel's two ways of taking a row's
+sum, at the sizes where their dispatch turns.
+
+The argmax kernel cuts rows into units of 512 16-byte vectors and gives waves spans of units, so
+the edges are rows of one vector, of a partial vector only, of one unit and one logit more, and
+batches whose spans cross rows and groups. The alpha kernel takes sums against offset 0 and
+retries a row whose sum leaves [2^-64, 2^64]: logits shifted by multiples of 40 cross both ends.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2510_20064_amd as hs
+
+pytestmark = pytest.mark.gpu
+
+DTYPES = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}
+
+
+def note(what):
+    print("\n[case] " + what, flush=True)
+
+
+def logits(shape, dtype, seed, kind):
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn(shape, generator=g) * 3.0
+    if kind == "ties":
+        x = x.round()
+    elif kind == "zeros":
+        x = x.sign() * 0.0  # +0 and -0 tie
+    elif kind == "masked":
+        x[torch.rand(shape, generator=g) < 0.4] = -float("inf")
+    elif kind == "nan":
+        x[torch.rand(shape, generator=g) < 0.02] = float("nan")
+    return x.to(DTYPES[dtype])
+
+
+def reference(x, V):
+    """Lowest index of each row's maximum, NaN ignored."""
+    z = x[..., :V].float().numpy()
+    z = np.where(np.isnan(z), -np.inf, z)
+    return np.argmax(z, axis=-1).astype(np.int32)
+
+
+@pytest.mark.parametrize("dtype", list(DTYPES))
+@pytest.mark.parametrize("kind", ["plain", "ties", "zeros", "masked", "nan"])
+@pytest.mark.parametrize("B,N,K,V", [
+    (1, 1, 1, 1), (2, 3, 2, 7), (1, 2, 1, 8), (3, 5, 2, 2049), (2, 8, 3, 4096), (2, 4, 1, 4097),
+    (1, 64, 2, 8200), (5, 7, 3, 33001), (24, 3, 2, 20011)])
+def test_argmax_and_agreement(B, N, K, V, kind, dtype):
+    note("argmax %s %s B=%d N=%d K=%d V=%d" % (dtype, kind, B, N, K, V))
+    x = logits((N + 1, B, K, (V + 7) // 8 * 8), dtype, 7 * V + N, kind)
+    x[N] = x[0]  # one drafter always agrees
+    ref = reference(x, V)
+    live = (x[..., :V] > -float("inf")).any(-1).numpy()
+    xd = x.to("cuda:0")
+    ws = hs.alloc_workspace(B, N, K, V, hs._dtype_code(xd), "cuda:0")
+    for mode in (hs.GREEDY, hs.SAMPLE, hs.GREEDY):  # one workspace, both kernels in turn
+        out = hs.eval_alpha(xd, V=V, temperature=1.0, mode=mode, want_agree=True,
+                            want_alpha=mode == hs.SAMPLE, want_argmax=True, workspace=ws)
+        torch.cuda.synchronize()
+        at = out["argmax_t"].cpu().numpy()
+        ad = out["argmax_d"].cpu().numpy()
+        rows, d = live[0], live[1:].transpose(1, 0, 2)
+        assert np.array_equal(at[rows], ref[0][rows])
+        assert np.array_equal(ad[d], ref[1:].transpose(1, 0, 2)[d])
+        agree = out["agree"].cpu().numpy()
+        assert np.array_equal(agree, (ad == at[:, None]).astype(np.uint8))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shift", [-120.0, -80.0, -40.0, 40.0, 80.0])
+@pytest.mark.parametrize("B,N,K,V", [(1, 8, 2, 4104), (1, 3, 2, 4104), (48, 8, 4, 32000)])
+def test_sums_outside_the_plain_range(B, N, K, V, shift, dtype):
+    # some rows shifted (a softmax does not see it), so that plain and retried rows share items;
+    # 48 queries run the pipelined kernel, one the kernel with one item per workgroup. A logit near
+    # 128 has an exponent rounded at 2^-18 (1.3e-5 of its term after the factor ln 2, twice for
+    # target and drafter, and a sum averages them): 2e-5 absolute, as for every alpha here
+    note("shift %g %s B=%d N=%d" % (shift, dtype, B, N))
+    x = logits((N + 1, B, K, V), "f32", 11, "plain")
+    x = (x * 8).round() / 8
+    x[1:] = (x[:1] + 0.5 * x[1:]).mul(4).round() / 4
+    x[0, :, 0] += shift
+    x[1, :, K - 1] += shift
+    x[N] += shift
+    x = x.to(DTYPES[dtype])
+    z = x.double()
+    p, q = torch.softmax(z[0], -1), torch.softmax(z[1:], -1)
+    ref = torch.minimum(p, q).sum(-1).permute(1, 0, 2)
+    out = hs.eval_alpha(x.to("cuda:0"), V=V, temperature=1.0, mode=hs.SAMPLE, want_alpha=True)
+    torch.cuda.synchronize()
+    err = (out["alpha"].cpu().double() - ref).abs().max().item()
+    assert err <= 2e-5, err
