@@ -8,9 +8,9 @@
 
 namespace hs {
 
-template <bool NEED_SUM, bool NEED_ARG>
+template <int WAVES, bool NEED_SUM, bool NEED_ARG>
 __device__ inline SliceStat block_reduce_stat(float m, int idx, float o, float s) {
-  __shared__ SliceStat sh[kWaves];
+  __shared__ SliceStat sh[WAVES];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     float m2 = __shfl_xor(m, off, 64);
@@ -31,7 +31,7 @@ __device__ inline SliceStat block_reduce_stat(float m, int idx, float o, float s
   __syncthreads();
   SliceStat r = sh[0];
 #pragma unroll
-  for (int w = 1; w < kWaves; ++w) {
+  for (int w = 1; w < WAVES; ++w) {
     SliceStat x = sh[w];
     if (NEED_ARG) argmax_combine(r.m, r.idx, x.m, x.idx);
     else r.m = fmaxf(r.m, x.m);

@@ -91,3 +91,19 @@ def test_sums_outside_the_plain_range(B, N, K, V, shift, dtype):
     torch.cuda.synchronize()
     err = (out["alpha"].cpu().double() - ref).abs().max().item()
     assert err <= 2e-5, err
+
+
+@pytest.mark.parametrize("dtype,rows", [("bf16", 1), ("bf16", 511), ("bf16", 512), ("f16", 3),
+                                        ("f32", 5), ("f32", 3071), ("f32", 3072)])
+@pytest.mark.parametrize("V", [3, 2050, 8193, 16391])
+def test_row_statistics_by_row_count(rows, V, dtype):
+    # fp32 sums of up to 16391 terms in a few hundred partial sums: relative 1e-6, over log terms
+    note("stats %s rows=%d V=%d" % (dtype, rows, V))
+    x = logits((rows, (V + 7) // 8 * 8), dtype, rows + V, "ties" if V == 2050 else "plain")
+    mx, lse, am = hs.softmax_stats(x.to("cuda:0"), V=V, temperature=0.7)
+    torch.cuda.synchronize()
+    z = x[:, :V].double()
+    assert torch.equal(mx.cpu().double(), z.amax(1))
+    assert np.array_equal(am.cpu().numpy(), np.argmax(x[:, :V].float().numpy(), axis=1))
+    ref = torch.logsumexp(z / 0.7, dim=1)
+    assert ((lse.cpu().double() - ref).abs() <= 1e-6 * (1 + ref.abs())).all()
