@@ -19,6 +19,9 @@ constexpr int kStep = 8;  // 16-byte loads of a unit per lane
 // Waves of a launch, when there are units enough: the device holds 4096 to 6144 of them at once, and
 // more and shorter spans only add arrivals (142 us with 4096 and 6144, 153 with 12288).
 constexpr int64_t kMinWaves = 4096;
+// Polls of an adder for its count to be opened (the opening wave comes first in dispatch order and
+// opens while its own first loads fly, so an adder hardly ever meets a count that is not open).
+constexpr uint32_t kOpenPolls = 1u << 10;
 
 struct ArgmaxArgs {
   int N, K, G;
@@ -94,13 +97,11 @@ __device__ __forceinline__ void fold_group(const ArgmaxArgs& A, int g, uint32_t 
     }
   }
   if (lane != 0) return;
-  // the last group to be folded advances the epoch; every count is left at 0 for the next tag
-  const uint32_t e0 = *A.epoch;
-  const uint32_t next = tag_of_epoch(e0 + 1u);
-  put_word(A.arrived + g, (uint64_t)next);
-  if (tagged_add(A.finished, tag) == (uint32_t)A.G - 1u) {
-    put_word(A.finished, (uint64_t)next);
-    *A.epoch = e0 + 1u;
+  // the last group to be folded advances the epoch and leaves its count open for the next call
+  if (tagged_add(A.finished, tag, kOpenPolls) == (uint32_t)A.G - 1u) {
+    const uint32_t e = *A.epoch + 1u;
+    put_word(A.finished, (uint64_t)tag_of_epoch(e));
+    *A.epoch = e;
   }
 }
 
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(kThreads, 4) void hs_argmax_kernel(ArgmaxArgs A) {
         const uint32_t waves = fdiv(gu + (uint32_t)(R * A.S) - 1u, A.div_span) -
                                fdiv(gu, A.div_span) + 1u;
         uint32_t n = 0;
-        if (lane == 0) n = tagged_add(A.arrived + g, tag);
+        if (lane == 0) n = tagged_add(A.arrived + g, tag, kOpenPolls);
         if ((uint32_t)__builtin_amdgcn_readfirstlane((int)n) == waves - 1u)
           fold_group<DT>(A, g, tag, lane);
       }
@@ -219,6 +220,13 @@ __global__ __launch_bounds__(kThreads, 4) void hs_argmax_kernel(ArgmaxArgs A) {
   };
   Raw x[kStep], y[kStep];
   load(x, true);
+  {  // the counts of the groups that begin in this span (and the first wave: the groups')
+    const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)tag_of_epoch(e0));
+    const int end = (int)fdiv((uint32_t)(uend - 1), A.div_group);
+    const bool begins = u == g * R * A.S;
+    if (u == 0 && lane == 63) open_count(A.finished, tag);
+    for (int i = (begins ? g : g + 1) + lane; i <= end; i += 64) open_count(A.arrived + i, tag);
+  }
   for (;;) {  // unrolled by two so that the register buffers alternate without copies
     if (!step(x, y)) break;
     if (!step(y, x)) break;
@@ -253,7 +261,7 @@ int launch_argmax(const TeamGeom& g, const RowTable& rows, uint8_t* agree, int32
   // the region of the team kernel's slice words: a row has at most as many pieces
   // as units, and no more units than slices (a slice is four wave loads), of three words each
   A.words = reinterpret_cast<uint64_t*>(ws + L.stat);
-  A.arrived = reinterpret_cast<uint64_t*>(ws + L.arrived);
+  A.arrived = reinterpret_cast<uint64_t*>(ws + L.arrived());
   A.argmax_t = argmax_t;
   A.argmax_d = argmax_d;
   A.agree = agree;

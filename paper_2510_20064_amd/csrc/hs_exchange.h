@@ -19,17 +19,29 @@ __device__ inline uint32_t call_tag(const uint32_t* epoch) {
 // count before (0 for the first add of a call): the word holds (count << 32) | tag, and a
 // word with another tag, from an earlier call or never written, counts as 0. So nothing has
 // to be reset between calls, and whatever a word held before cannot skew this call's count.
-// The call that completes a count leaves the word at (0 << 32) | the next call's tag
-// (count_team), so each add of the next call is a single fetch-and-add, which leaves the tag
-// half alone and costs every adder one round trip however many add at once. An add that
-// finds another tag (the first call on a zeroed workspace) goes on by compare-and-swap: the
-// first exchange replaces the whole word, so its earlier fetch-and-adds on the stale word do
-// not count, and every adder is counted once, by its fetch-and-add or by its exchange.
-__device__ inline uint32_t tagged_add(uint64_t* w, uint32_t tag) {
-  const uint64_t old =
-      __hip_atomic_fetch_add(w, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((uint32_t)old == tag) return (uint32_t)(old >> 32);
-  uint64_t cur = get_word(w);
+// Once the word carries the call's tag, an add is a single fetch-and-add, which leaves the tag
+// half alone and costs every adder one round trip however many add at once. The tag gets there
+// beforehand: the control block's count is left at (0 << 32) | the next call's tag by the call
+// that completes it; a count anywhere else must not be (another shape keeps other words there,
+// which would then look current), and is opened by one wave of the call itself (open_count).
+// An add that finds another tag polls for the opening up to `polls` times (its own add went to
+// the stale word, which the opening replaces as a whole) and then adds again, or goes on by
+// compare-and-swap: the first exchange replaces the whole word, so every adder is counted once,
+// by its fetch-and-add on the open word or by its exchange. (Looking at the word before the add
+// instead makes every add two operations on it, which queue: 24 groups of 142 adders took
+// 114 us for 68.)
+__device__ inline uint32_t tagged_add(uint64_t* w, uint32_t tag, uint32_t polls = 0) {
+  auto add = [&]() {
+    return __hip_atomic_fetch_add(w, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  uint64_t cur = add();
+  if ((uint32_t)cur == tag) return (uint32_t)(cur >> 32);
+  cur = get_word(w);
+  for (uint32_t n = 0; n < polls && (uint32_t)cur != tag; ++n) {
+    __builtin_amdgcn_s_sleep(kPollSleep);
+    cur = get_word(w);
+  }
+  if ((uint32_t)cur == tag) return (uint32_t)(add() >> 32);  // the tag stays for the call
   for (;;) {  // each failed exchange means another add succeeded: this ends
     const uint32_t n = (uint32_t)cur == tag ? (uint32_t)(cur >> 32) : 0u;
     uint64_t expect = cur;
@@ -38,6 +50,15 @@ __device__ inline uint32_t tagged_add(uint64_t* w, uint32_t tag) {
                                              __HIP_MEMORY_SCOPE_AGENT))
       return n;
     cur = expect;
+  }
+}
+
+// Opens the count at w for the call with this tag, if no adder has done so yet.
+__device__ inline void open_count(uint64_t* w, uint32_t tag) {
+  uint64_t cur = get_word(w);
+  while ((uint32_t)cur != tag &&  // each failed exchange means an add succeeded: this ends
+         !__hip_atomic_compare_exchange_strong(w, &cur, (uint64_t)tag, __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
   }
 }
 

@@ -207,9 +207,9 @@ struct TeamWs {
   size_t norm_copy;  // bytes of one copy of them (kNormCopies - 1 more follow the gamma words)
   size_t part;   // [G][N][S] words: per-slice sums of min(p, q_i)
   size_t gw;     // [B][N][K] words: gamma (alpha or agreement) for a learner in the same launch
-  size_t arrived;  // [G] tagged counts of the argmax kernel (a region of their own: a count is
-                   // left with the next call's tag)
   size_t total;
+  // the argmax kernel's [G] tagged counts: it has no normalisers (and more rows than groups)
+  size_t arrived() const { return norm; }
 };
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -240,8 +240,6 @@ inline TeamWs team_ws(const TeamGeom& g) {
   L.gw = off;
   off = align256(off + 8 * (size_t)g.B * g.N * g.K);
   off += (kNormCopies - 1) * L.norm_copy;  // the normaliser words' other copies
-  L.arrived = off;
-  off = align256(off + 8 * (size_t)g.G);
   L.total = off;
   return L;
 }

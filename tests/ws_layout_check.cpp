@@ -37,6 +37,8 @@ int main() {
     CHECK(L.norm_copy % 256 == 0 && L.norm_copy >= 24 * sets * rows);
     CHECK(L.part >= L.norm + L.norm_copy);
     CHECK(L.gw >= L.part + 8 * (size_t)g.G * g.N * g.S);
+    // the argmax kernel's counts lie in the normaliser region
+    CHECK(L.arrived() >= L.norm && L.arrived() + 8 * (size_t)g.G <= L.part);
     CHECK(L.total >= hs::align256(L.gw + 8 * (size_t)g.B * g.N * g.K) +
                          (size_t)(hs::kNormCopies - 1) * L.norm_copy);
     // the tag of every epoch is 31-bit and never 0 (the content of a zeroed workspace)
