@@ -152,20 +152,39 @@ __device__ inline uint64_t word_of_bits(uint32_t x, uint32_t tag) {
   return ((uint64_t)x << 32) | tag;
 }
 
-// Words of a row of a row set: S slice maxima (with an argmax, or where a sum is shifted), S
-// exp2 sums, S argmaxes. Each kind is contiguous, so that a fold's lanes read whole lines.
+// A thread's offset for the exp2 sum of its logits of a row, m the largest of them: integer-valued
+// and at or above m c (exp_offset_of), so that sums against different offsets rescale exactly and
+// no exponent is positive. Held to [-2^29, 2^29], where differences of offsets fit an int32: beyond
+// it (logits far outside the range of |z c| <= 2^28) terms are 0 at the lower end and a sum
+// infinite at the upper, and without a logit whose scaled value is finite (m c = -inf: the fma
+// then gives NaN, as for a NaN m, and fmaxf the lower end) every term is 0, or NaN for a NaN logit.
+constexpr int kNoOffset = -(1 << 29);
+__device__ inline float thread_offset(float m, float c) {
+  const float mc = m * c;
+  return fminf(fmaxf(ceilf(fmaf(fabsf(mc), 0x1p-22f, mc)), (float)kNoOffset), 0x1p29f);
+}
+
+// Words of a row of a row set: S slice maxima (with an argmax, or where a sum is shifted; the
+// single-item kernel without an argmax: S slice offsets), S exp2 sums, S argmaxes. Each kind is contiguous, so that a fold's lanes read whole lines.
 __device__ inline uint64_t* stat_row(const TeamArgs& A, int set, int r, int RM) {
   return A.stat + ((int64_t)set * RM + r) * A.S * 3;
 }
 
-// Log2 normaliser o + l2 of row rr (o integer-valued, l2 small; retry: the retry mark instead) as
-// an unevaluated sum hi + lo (TwoSum); lane c writes copy c.
+// Log2 normaliser o + log2(sum) of row rr, o integer-valued (retry: the retry mark instead) as an
+// unevaluated sum hi + lo; lane c writes copy c. The sum's exponent is taken apart (exactly, also
+// from a large o): the logarithm then lies in [-1, 0), where its error is smallest.
 template <int D, int NC>
 __device__ __forceinline__ void publish_norm(const TeamArgs& A, int set, int rr, float o,
-                                             float l2, bool retry, uint32_t tt, int lane) {
-  const float hi = o + l2;
-  const float bb = hi - o;
-  const float lo = (o - (hi - bb)) + (l2 - bb);
+                                             float sum, bool retry, uint32_t tt, int lane) {
+  auto two_sum = [](float a, float b, float& err) {
+    const float s = a + b, bb = s - a;
+    err = (a - (s - bb)) + (b - bb);
+    return s;
+  };
+  float e0, e1;
+  const float n = two_sum(o, (float)__builtin_amdgcn_frexp_expf(sum), e0);
+  const float hi = two_sum(n, log2f(__builtin_amdgcn_frexp_mantf(sum)), e1);
+  const float lo = e0 + e1;
   if (lane < NC) {
     uint64_t* cw = norm_copy(A, lane, D + 1) + ((int64_t)set * (D + 1) + rr) * 3;
     put_word(cw, word_of_bits(retry ? kRetry : plain_nan(hi), tt));
@@ -174,7 +193,7 @@ __device__ __forceinline__ void publish_norm(const TeamArgs& A, int set, int rr,
 }
 
 // The fold of a retried row: its S shifted sums, each against its own offset.
-template <int D, int NC>
+template <int D>
 __device__ __forceinline__ void fold_retried(const TeamArgs& A, int set, int rr, uint32_t tag,
                                              int lane) {
   const uint64_t* base = stat_row(A, set, rr, D + 1);
@@ -189,21 +208,22 @@ __device__ __forceinline__ void fold_retried(const TeamArgs& A, int set, int rr,
                  __uint_as_float((uint32_t)(w >> 32) & ~kShifted));
   }
   wave_lse(o, sum);
-  publish_norm<D, NC>(A, set, rr, o, log2f(sum), false, tag | taint_bits(__ballot(lost) != 0), lane);
+  publish_norm<D, 1>(A, set, rr, o, sum, false, tag | taint_bits(__ballot(lost) != 0), lane);
 }
 
 // Fold of row rr of row set `set`: the S slice statistics, two slices per lane per pass
 // (lane j takes slices j, j + 64, ... in order), then the wave. Publishes the row's log2
 // normaliser as hi + lo (in NC copies) and its argmax; writes the argmax and agreement
-// outputs. The published words are tainted when any slice word was lost.
-template <int D, bool NEED_ARG, int NC = 1>
+// outputs. The published words are tainted when any slice word was lost. OWN: every slice's sum is
+// against an offset of its own.
+template <int D, bool NEED_ARG, bool OWN, int NC = 1>
 __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int b, int k, int sub,
                                 uint32_t tag, int lane) {
   constexpr int RM = D + 1;
   const int S = A.S;
   const uint64_t* base = stat_row(A, set, rr, RM);
   float m = -INFINITY, sum = 0.0f;
-  int idx = INT_MAX;
+  int idx = INT_MAX, o = kNoOffset;
   bool lost = false;
   for (int j0 = 0; j0 < S; j0 += 128) {
     uint64_t w[2][3];
@@ -211,7 +231,7 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
     for (int h = 0; h < 2; ++h) {  // issue every load of the pass before waiting on any
       const int j = j0 + lane + 64 * h;
       if (j < S) {
-        if (NEED_ARG) w[h][0] = get_word(base + j);
+        if (NEED_ARG || OWN) w[h][0] = get_word(base + j);
         w[h][1] = get_word(base + S + j);
         if (NEED_ARG) w[h][2] = get_word(base + 2 * S + j);
       }
@@ -220,26 +240,39 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
     for (int h = 0; h < 2; ++h) {
       const int j = j0 + lane + 64 * h;
       if (j < S) {
-        if (NEED_ARG) {
+        if (NEED_ARG || OWN) {
           if (tag_of(w[h][0]) != tag) w[h][0] = await_word(base + j, tag, A);
+          lost |= tainted(w[h][0]);
+        }
+        if (NEED_ARG) {
           if (tag_of(w[h][2]) != tag) w[h][2] = await_word(base + 2 * S + j, tag, A);
-          lost |= tainted(w[h][0]) || tainted(w[h][2]);
+          lost |= tainted(w[h][2]);
           argmax_combine(m, idx, word_f(w[h][0]), word_i(w[h][2]));
         }
         if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + S + j, tag, A);
         lost |= tainted(w[h][1]);
-        sum += word_f(w[h][1]);
+        if (OWN) {
+          const int oj = NEED_ARG ? (int)thread_offset(word_f(w[h][0]), A.c) : word_i(w[h][0]);
+          const int on = max(o, oj);
+          sum = ldexpf(sum, o - on) + ldexpf(word_f(w[h][1]), oj - on);
+          o = on;
+        } else {
+          sum += word_f(w[h][1]);
+        }
       }
     }
   }
   if (NEED_ARG) wave_max<true>(m, idx);
   const bool any_lost = __ballot(lost) != 0;
   const uint32_t tt = tag | taint_bits(any_lost);
+  float ro = A.o;
+  if (OWN) {
+    const int on = wave_max_i(o);
+    sum = ldexpf(sum, o - on);
+    ro = (float)on;
+  }
   sum = wave_sum_f(sum);
-  // the sum's exponent apart: the logarithm then lies in [-1, 0), where its error is smallest
-  publish_norm<D, NC>(A, set, rr, A.o + (float)__builtin_amdgcn_frexp_expf(sum),
-                      log2f(__builtin_amdgcn_frexp_mantf(sum)),
-                      !any_lost && !sum_in_range(sum), tt, lane);
+  publish_norm<D, NC>(A, set, rr, ro, sum, !OWN && !any_lost && !sum_in_range(sum), tt, lane);
   uint64_t* nw = A.norm + ((int64_t)set * RM + rr) * 3;
   if (lane != 0) return;
   if (NEED_ARG) {
@@ -288,19 +321,21 @@ __device__ inline ItemPos item_pos(const TeamArgs& A, uint32_t set, int slot, in
 // so that one 16-lane group reduces one row (group_read) instead of every wave reducing every
 // row on its own.
 constexpr uint32_t kWide = 0x80000000u;
-template <int D, bool NEED_ARG>
+template <int D, bool NEED_ARG, bool SINGLE>
 struct TeamLds {
-  float xs[D + 1][kThreads];                     // per-thread exp2 sums (retry: max keys)
-  float xt[NEED_ARG ? D + 1 : 1][kThreads];   // per-thread maxima
-  int xi[NEED_ARG ? D + 1 : 1][kThreads];     // per-thread argmax
-  float xp[D][kThreads];                      // per-thread min-sums of each drafter
-  float o[D + 1];  // retry, kept e_v: the slice offset that each row's are taken against
+  float xs[D + 1][kThreads];                    // per-thread exp2 sums (retry: max keys; SINGLE:
+                                                // later the min-sums of the drafters)
+  int xo[SINGLE ? D + 1 : 1][kThreads];         // SINGLE: the offsets that they are taken against
+  float xt[NEED_ARG ? D + 1 : 1][kThreads];     // per-thread maxima
+  int xi[NEED_ARG ? D + 1 : 1][kThreads];       // per-thread argmax
+  float xp[SINGLE ? 1 : D][kThreads];           // per-thread min-sums of each drafter
+  int n[D + 1];     // SINGLE: the rows' rint(hi)
+  float G[D];      // SINGLE: 2^(a_t - a_d)
   float no[D + 1];  // retry: minus the slice offset, then (wide form) minus the row offset
   float nw[D];     // plain: the exponent addend of drafter d
   float dl[D];     // wide: a_t - a_d
   uint32_t form;   // 0: plain; kWide: wide; else the item's rows to retry (bit 2 r)
-  float G[D];      // kept e_v: 2^(a_t - a_d)
-  float F[D];      // factor of drafter d's group sum: 2^(a_d) (kept e_v), else 2^(a_t)
+  float F[D];      // factor of drafter d's group sum, 2^(a_t); SINGLE: 2^(a_d)
   uint32_t next;  // a row set of the team's coming items, posted by thread 0
   uint32_t taint;  // the item's normalisers include a lost word: its partials are tainted
   // the row table, copied from the kernel arguments once (lane-parallel loads instead of a
@@ -442,8 +477,18 @@ __device__ __forceinline__ void launder(Raw& x) {
   __builtin_memcpy(&x, w, 16);
 }
 
+// Largest of a thread's logits of one row; NaN when one of them is.
+template <int E>
+__device__ __forceinline__ float max_or_nan(const float (&z)[E]) {
+  float m = maximum3(z[0], z[1], z[2]);
+#pragma unroll
+  for (int e = 3; e < E; e += 2) m = maximum3(m, z[e], e + 1 < E ? z[e + 1] : z[e]);
+  return m;
+}
+
 // ---- 1. per-thread statistics of every row of item q in one pass, to LDS: the exp2 sum (KEPT:
-// the e_v stay in x) and, with NEED_ARG, the max and its lowest index ----
+// against the thread's own offset, and the e_v stay in x) and, with NEED_ARG, the max and its
+// lowest index ----
 template <int DT, int D, bool NEED_ARG, bool KEPT, typename L, typename X>
 __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q,
                                              typename Vec<DT>::Raw (&raw)[D + 1], X& x, L& sh,
@@ -455,8 +500,8 @@ __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q
     launder(raw[r]);
     float z[E];
     Vec<DT>::unpack(raw[r], z);
+    float m = -INFINITY;
     if (NEED_ARG) {
-      float m = -INFINITY;
       int idx = INT_MAX;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
@@ -470,10 +515,16 @@ __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q
       sh.xt[r][t] = m;
       sh.xi[r][t] = idx;
     }
+    float of = A.o;
+    if constexpr (KEPT) {
+      if (!NEED_ARG) m = max_or_nan(z);
+      of = thread_offset(m, A.c);
+      sh.xo[r][t] = (int)of;
+    }
     float v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      v[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, -A.o));
+      v[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, -of));
       if constexpr (KEPT) x[r][e] = v[e];
     }
     sh.xs[r][t] = sum_elems(v);
@@ -509,44 +560,63 @@ __device__ __forceinline__ float group_sum(const L& sh, int n, int gi, int gl) {
 // falling on the same few members every time (the team goes at its slowest member's pace).
 __device__ inline int duty_index(int s, int rot, int S) { return s >= rot ? s - rot : s - rot + S; }
 
-// Reduces and publishes the slice statistics of item q as tagged words.
-template <bool NEED_ARG, typename L>
+// Reduces and publishes the slice statistics of item q as tagged words (OWN: the threads' sums are
+// against offsets of their own, and the slice's sum is published against the largest of them,
+// beside it; with an argmax that offset follows from the maximum).
+template <bool NEED_ARG, bool OWN, typename L>
 __device__ __forceinline__ void publish_stats(const TeamArgs& A, const ItemPos& q, uint32_t tag,
                                               int RM, L& sh, int gi, int gl) {
   float m = 0.0f;
   int idx = 0;
   if (NEED_ARG) group_argmax(sh, q.n, gi, gl, m, idx);
-  const float s = group_sum(sh, q.n, gi, gl);
+  float s;
+  int o = 0;
+  if constexpr (OWN) {
+    const int r = min(gi, q.n);
+    int ov[16];
+    group_read(&sh.xo[r][0], gl, ov);
+    o = ov[0];
+#pragma unroll
+    for (int u = 1; u < 16; ++u) o = max(o, ov[u]);
+    o = row16_max(o);
+    float v[16];
+    group_read(&sh.xs[r][0], gl, v);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = ldexpf(v[u], ov[u] - o);
+    s = row16_sum(sum16(v));
+  } else {
+    s = fabsf(group_sum(sh, q.n, gi, gl));  // (a NaN's sign)
+  }
   if (gl != 0 || gi > q.n) return;
   uint64_t* wp = stat_row(A, q.set, gi, RM) + q.s;
   if (NEED_ARG) {
     put_word(wp, word_of(m, tag));
     put_word(wp + 2 * A.S, word_of(idx, tag));
+  } else if (OWN) {
+    put_word(wp, word_of(o, tag));
   }
-  put_word(wp + A.S, word_of(fabsf(s), tag));  // (a NaN's sign)
+  put_word(wp + A.S, word_of(s, tag));
 }
 
 // ---- 4. fold duty: rows i, i + S, ... of the row set (i = the slot's duty index for the
 // item's rotation rot), spread over the waves, wave `first` taking the first ----
-template <int D, bool NEED_ARG, int NC = 1>
+template <int D, bool NEED_ARG, bool OWN, int NC = 1>
 __device__ __forceinline__ void fold_item(const TeamArgs& A, const ItemPos& q, uint32_t tag,
                                           int lane, int wv, int first, int rot = 0) {
   const int order = (wv + kWaves - first) % kWaves;
   for (int rr = duty_index(q.s, rot, A.S) + order * A.S; rr <= q.n; rr += kWaves * A.S)
-    fold_row<D, NEED_ARG, NC>(A, q.set, rr, q.b, q.k, q.sub, tag, lane);
+    fold_row<D, NEED_ARG, OWN, NC>(A, q.set, rr, q.b, q.k, q.sub, tag, lane);
 }
 
 // ---- 5. normalisers L = hi + lo (the duty wave; a barrier follows): lanes 2r and 2r + 1 wait for
-// row r's hi and lo; lane 2r forms a_r = (o_r - hi_r) - lo_r, o_r the offset of the row's
-// exponents, and, for a drafter row, the constants of its min-sum to LDS. Differences of the
-// a_r are taken part by part, so that they lose nothing to a large hi.
-// o_r = A.o, except after a retry (AGAIN, every normaliser final), where it is the slice's offset
-// with kept e_v and rint(hi_r) in the wide form.
-// KEPT (6'): G = 2^(a_t - a_d) and F = 2^(a_d). Else (6): exponent addend nw = -A.o - (a_t - a_d), or
-// the difference itself in the wide form, and F = 2^(a_t).
-// A row with no finite logit folds to hi = -inf, lo = NaN, so its a is NaN: it has no
-// distribution, and F is NaN whenever a_t or a_d is, which makes that drafter's alpha NaN in
-// every form. ----
+// row r's hi and lo. A row with no finite logit folds to hi = -inf, lo = NaN: it has no
+// distribution, which makes alpha NaN for that drafter, or for every drafter of that target.
+// Lane 2r forms a_r = (o_r - hi_r) - lo_r, o_r = rint(hi_r) with KEPT and in the wide form (after a
+// retry, AGAIN, every normaliser final), else A.o, the offset of the row's exponents, and for a
+// drafter row the constants of its min-sum. KEPT (6'): o_r, G = 2^(a_t - a_d) and F = 2^(a_d). Else
+// (6): exponent addend nw = -A.o - (a_t - a_d), or the difference itself in the wide form, and
+// F = 2^(a_t). Differences of the a_r are taken part by part, so that they lose nothing to a large
+// hi. ----
 template <int D, bool KEPT, bool AGAIN, typename L>
 __device__ __forceinline__ void await_norms(const TeamArgs& A, const ItemPos& q, uint32_t tag,
                                             L& sh, int lane) {
@@ -562,21 +632,16 @@ __device__ __forceinline__ void await_norms(const TeamArgs& A, const ItemPos& q,
     lost = tainted(w);
   }
   const bool any_lost = __ballot(lost) != 0;
+  if (lane == 0) sh.taint = taint_bits(any_lost);
   const bool row = !(lane & 1) && lane < 2 * (q.n + 1);
   const uint64_t retry = __ballot(row && __float_as_uint(h) == kRetry);
-  if (lane == 0) {
-    sh.taint = taint_bits(any_lost);
-    sh.form = AGAIN ? kWide : (uint32_t)retry;
-  }
+  if (!KEPT && lane == 0) sh.form = AGAIN ? kWide : (uint32_t)retry;
   const float lo = dpp_f<0xB1>(h);  // lane 2r: the lo of row r, from lane 2r + 1
   float o = A.o;
-  if (AGAIN && row) {
-    if (KEPT) {
-      o = sh.o[lane >> 1];
-    } else {
-      o = rintf(h);
-      sh.no[lane >> 1] = fabsf(o) < INFINITY ? -o : 0.0f;
-    }
+  if ((KEPT || AGAIN) && row) {
+    o = rintf(h);
+    if (KEPT) sh.n[lane >> 1] = cvt_i32_sat(o);
+    else sh.no[lane >> 1] = fabsf(o) < INFINITY ? -o : 0.0f;
   }
   const float x = o - h;
   const float xt = lane_f(x, 0), lot = lane_f(lo, 0);
@@ -587,7 +652,7 @@ __device__ __forceinline__ void await_norms(const TeamArgs& A, const ItemPos& q,
     const float diff = (xt - x) - (lot - lo);  // a_t - a_d
     if (KEPT) {
       sh.G[d] = __builtin_amdgcn_exp2f(diff);
-      sh.F[d] = undefined ? NAN : exp2_split(x, lo);
+      sh.F[d] = undefined ? NAN : __builtin_amdgcn_exp2f(a);
     } else {
       sh.nw[d] = -A.o - diff;
       if (AGAIN) sh.dl[d] = diff;
@@ -602,11 +667,10 @@ __device__ __forceinline__ void await_norms(const TeamArgs& A, const ItemPos& q,
 // value is finite), published with the maximum; then the folds, and all normalisers. The whole
 // workgroup calls this after a barrier, and it ends with one. Every member of the team comes
 // here for the same item, before it waits for any word of a later one, so the waits end. The
-// logits come from memory again (rare rows are not worth registers). KEPT: the rows' e_v in x
-// follow. ----
-template <int DT, int D, bool KEPT, int NC, typename L, typename X>
+// logits come from memory again (rare rows are not worth registers). ----
+template <int DT, int D, typename L>
 __device__ __forceinline__ void retry_item(const TeamArgs& A, const ItemPos& q, uint32_t form,
-                                           uint32_t tag, X& x, L& sh, int t, int first, int rot) {
+                                           uint32_t tag, L& sh, int t, int first, int rot) {
   using Vt = Vec<DT>;
   constexpr int E = Vt::kElems;
   const int lane = t & 63, wv = t >> 6, gi = t >> 4, gl = t & 15;
@@ -637,25 +701,16 @@ __device__ __forceinline__ void retry_item(const TeamArgs& A, const ItemPos& q, 
 #pragma unroll
     for (int u = 1; u < 16; ++u) k = max(k, kv[u]);
     m = fkey_inv(row16_max(k));
-    if (gl == 0 && gi <= q.n) {
-      const float o = exp_offset_of(m, A.c);
-      if (KEPT) sh.o[gi] = mine ? o : A.o;
-      sh.no[gi] = -exp_offset(o);
-    }
+    if (gl == 0 && gi <= q.n) sh.no[gi] = -exp_offset(exp_offset_of(m, A.c));
   }
   __syncthreads();
-#pragma unroll(KEPT ? D + 1 : 1)
-  for (int r = 0; r <= D; ++r) {
-    if (((form >> (2 * r)) & 1u) == 0) continue;  // (bits past row n are 0)
+  for (int r = 0; r <= q.n; ++r) {
+    if (((form >> (2 * r)) & 1u) == 0) continue;
     float z[E];
     load(r, z);
     const float no = sh.no[r];
 #pragma unroll
     for (int e = 0; e < E; ++e) z[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, no));
-    if constexpr (KEPT) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) x[r][e] = z[e];
-    }
     sh.xs[r][t] = sum_elems(z);
   }
   __syncthreads();
@@ -669,26 +724,34 @@ __device__ __forceinline__ void retry_item(const TeamArgs& A, const ItemPos& q, 
   }
   const int order = (wv + kWaves - first) % kWaves;
   for (int rr = duty_index(q.s, rot, A.S) + order * A.S; rr <= q.n; rr += kWaves * A.S)
-    if ((form >> (2 * rr)) & 1u) fold_retried<D, NC>(A, q.set, rr, tag, lane);
-  if (wv == first) await_norms<D, KEPT, true>(A, q, tag, sh, lane);
+    if ((form >> (2 * rr)) & 1u) fold_retried<D>(A, q.set, rr, tag, lane);
+  if (wv == first) await_norms<D, false, true>(A, q, tag, sh, lane);
   __syncthreads();
 }
 
-// ---- 6'. per-thread min-sums from kept e_v: min(p_v, q_v) = 2^(a_d) min(e_t,v G, e_d,v) with
-// G = 2^(a_t - a_d); one multiply, one min and one add per drafter logit ----
+// ---- 6'. per-thread min-sums from kept e_v: with b_r the thread's offset of row r less the
+// integer part n_r of the row's normaliser, p_v = e_t,v 2^(b_t + a_t), q_v = e_d,v 2^(b_d + a_d), so
+// min(p_v, q_v) = F 2^(b_d) min(e_t,v G 2^(b_t - b_d), e_d,v); one multiply, one min and one add per
+// drafter logit. The offset is that of the thread's largest logit, so 2^(b_r) is about the largest
+// probability the thread holds: where the factor of e_t overflows, q's share is below 2^-126, and
+// where it underflows p's is. A thread without a finite logit of a row has 2^(b_r) = 0. ----
 template <int DT, int D, typename L>
 __device__ __forceinline__ void thread_minsums_kept(const ItemPos& q,
                                                     const float (&x)[D + 1][Vec<DT>::kElems],
                                                     L& sh, int t) {
   constexpr int E = Vec<DT>::kElems;
+  // (n_r saturates for a row without a distribution, whose F is NaN)
+  auto less = [](int a, int b) { return (int)((uint32_t)a - (uint32_t)b); };
+  const int bt = less(sh.xo[0][t], sh.n[0]);
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     if (d >= q.n) continue;
-    const float G = sh.G[d];
+    const int bd = less(sh.xo[d + 1][t], sh.n[d + 1]);
+    const float G = ldexpf(sh.G[d], less(bt, bd));
     float y[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) y[e] = min_pos(x[0][e] * G, x[d + 1][e]);
-    sh.xp[d][t] = sum_elems(y);
+    sh.xs[d][t] = sum_elems(y) * ldexpf(sh.F[d], bd);
   }
 }
 
@@ -873,7 +936,7 @@ template <int DT, int D, bool NEED_ARG, bool SINGLE>
 __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team_kernel(TeamArgs A) {
   using Raw = typename Vec<DT>::Raw;
   constexpr int RM = D + 1;
-  __shared__ TeamLds<D, NEED_ARG> sh;
+  __shared__ TeamLds<D, NEED_ARG, SINGLE> sh;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int gi = t >> 4, gl = t & 15;  // 16-lane group gi reduces row gi; gl: lane in it
   const int S = A.S;
@@ -928,7 +991,7 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     thread_stats<DT, D, NEED_ARG, false>(A, q, raw, sh, sh, t);
     __syncthreads();
     if (wv * 4 <= q.n)  // this wave holds the group of a row
-      publish_stats<NEED_ARG>(A, q, tag, RM, sh, gi, gl);
+      publish_stats<NEED_ARG, false>(A, q, tag, RM, sh, gi, gl);
     __builtin_amdgcn_s_setprio(0);
   };
   // the item's slice partials to the workspace (after a barrier), as tagged words
@@ -936,11 +999,12 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     if (wv * 4 < q.n) {
       float v[16];
       const int d = min(gi, q.n - 1);
-      group_read(&sh.xp[d][0], gl, v);
-      const float y = row16_sum(sum16(v));
+      group_read(SINGLE ? &sh.xs[d][0] : &sh.xp[d][0], gl, v);
+      float y = row16_sum(sum16(v));
+      if (!SINGLE) y *= sh.F[d];
       if (gl == 0 && gi < q.n)
         put_word(A.part + ((int64_t)q.g * A.N + q.sub * D + gi) * S + q.s,
-                 word_of(y * sh.F[gi], tag | sh.taint));
+                 word_of(y, tag | sh.taint));
     }
   };
 
@@ -981,8 +1045,8 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     mask_tail<DT, D>(A, q, R0);
     thread_stats<DT, D, NEED_ARG, true>(A, q, R0, x, sh, t);
     __syncthreads();
-    if (wv * 4 <= q.n) publish_stats<NEED_ARG>(A, q, tag, RM, sh, gi, gl);
-    fold_item<D, NEED_ARG, kNormCopies>(A, q, tag, lane, wv, 0);
+    if (wv * 4 <= q.n) publish_stats<NEED_ARG, true>(A, q, tag, RM, sh, gi, gl);
+    fold_item<D, NEED_ARG, true, kNormCopies>(A, q, tag, lane, wv, 0);
     __builtin_amdgcn_s_setprio(0);
     // with one item per workgroup the leader counts its team once it has folded row 0 (every
     // member has published, so has read the tag), not at its end: the count's round trip
@@ -991,8 +1055,6 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     if (leader && t == 0) count_team(A, tag, teams);
     if (wv == 0) await_norms<D, true, false>(A, q, tag, sh, lane);
     __syncthreads();
-    const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
-    if (form) retry_item<DT, D, true, kNormCopies>(A, q, form, tag, x, sh, t, 0, 0);
     thread_minsums_kept<DT, D>(q, x, sh, t);
     __syncthreads();
     store_partials(q);
@@ -1029,7 +1091,7 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     if (claiming)
       cv = __hip_atomic_fetch_add(A.next_set, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_s_setprio(kFoldPrio);
-    fold_item<D, NEED_ARG>(A, q, tag, lane, wv, kDutyWave, rotation(set, 0));
+    fold_item<D, NEED_ARG, false>(A, q, tag, lane, wv, kDutyWave, rotation(set, 0));
     __builtin_amdgcn_s_setprio(0);
     if (claiming)
       put_word(mbox + ((j + 3) & 3),
@@ -1041,7 +1103,7 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     __syncthreads();
     const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
     if (form)
-      retry_item<DT, D, false, 1>(A, q, form, tag, sh, sh, t, kDutyWave, rotation(set, 0));
+      retry_item<DT, D>(A, q, form, tag, sh, t, kDutyWave, rotation(set, 0));
     thread_minsums<DT, D>(A, q, rc, sh, t);
     __syncthreads();
     store_partials(q);
@@ -1112,7 +1174,7 @@ int launch_t(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* learned) {
   if (A.learn) {
     const size_t need = sizeof(double) * (size_t)tail_lds_doubles(A.tail) +
                         sizeof(float) * (size_t)g.N * g.K;
-    if (need > sizeof(TeamLds<D, NA>)) A.learn = 0;
+    if (need > (single ? sizeof(TeamLds<D, NA, true>) : sizeof(TeamLds<D, NA, false>))) A.learn = 0;
   }
   *learned = A.learn != 0;
   A.teams = (int)teams;

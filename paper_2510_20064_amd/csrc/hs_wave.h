@@ -69,6 +69,16 @@ __device__ inline float wave_sum_f(float v) {
   return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
 }
 
+// Wave max of an int.
+__device__ inline int wave_max_i(int k) {
+  k = max(k, dpp_i<0xB1>(k));
+  k = max(k, dpp_i<0x4E>(k));
+  k = max(k, dpp_i<0x141>(k));
+  k = max(k, dpp_i<0x140>(k));
+  return max(max(__builtin_amdgcn_readlane(k, 0), __builtin_amdgcn_readlane(k, 16)),
+             max(__builtin_amdgcn_readlane(k, 32), __builtin_amdgcn_readlane(k, 48)));
+}
+
 template <int CTRL>
 __device__ inline void argmax_step(float& m, int& idx) {
   const float m2 = dpp_f<CTRL>(m);
@@ -91,14 +101,7 @@ __device__ inline void wave_max(float& m, int& idx) {
     m = r;
     idx = ri;
   } else {  // m not NaN
-    int k = fkey(m);
-    k = max(k, dpp_i<0xB1>(k));
-    k = max(k, dpp_i<0x4E>(k));
-    k = max(k, dpp_i<0x141>(k));
-    k = max(k, dpp_i<0x140>(k));
-    k = max(max(__builtin_amdgcn_readlane(k, 0), __builtin_amdgcn_readlane(k, 16)),
-            max(__builtin_amdgcn_readlane(k, 32), __builtin_amdgcn_readlane(k, 48)));
-    m = fkey_inv(k);
+    m = fkey_inv(wave_max_i(fkey(m)));
   }
 }
 
