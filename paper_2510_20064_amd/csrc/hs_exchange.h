@@ -87,22 +87,6 @@ __device__ inline uint64_t await_word(const uint64_t* w, uint32_t tag, const ARG
   return v;
 }
 
-// The word at w once it carries tag and SKIP(value bits) is false (bounded as await_word).
-template <typename ARGS, typename SKIP>
-__device__ inline uint64_t await_value(const uint64_t* w, uint32_t tag, const ARGS& A,
-                                       SKIP skip) {
-  uint64_t v = await_word(w, tag, A);
-  for (uint32_t n = 1; !tainted(v) && skip((uint32_t)(v >> 32)); ++n) {
-    if (n >= A.polls || ((n & 255) == 0 && (uint32_t)get_word(A.fail) == tag)) {
-      put_word(A.fail, word_of(1, tag));
-      return (0xFFFFFFFEull << 32) | kTaint | tag;
-    }
-    __builtin_amdgcn_s_sleep(kPollSleep);
-    v = await_word(w, tag, A);
-  }
-  return v;
-}
-
 // Largest of a thread's logits of one row, NaN ignored (-inf when there is no other), -0 as +0.
 // v_maximum3_f32 takes two logits per instruction and returns NaN when it meets one, whatever
 // its payload; such a lane then takes the slow way.

@@ -8,11 +8,13 @@
 // one (query, position) group, 256 16-byte vectors each, held in the registers of one
 // 256-thread workgroup (thread t owns vector t of every row). The S items of a row set form
 // a team that is resident at the same time:
-//   1. every item reduces its rows (max, lowest argmax, exp2 sum against the slice offset
-//      o, an integer-valued float at or above m c, c = log2(e) / T) and publishes them as
-//      tagged words;
+//   1. every item takes its rows' exp2 sums (z c, c = log2(e) / T, less an integer-valued offset:
+//      the thread's own, at or above its largest z c, or one common to the call) and, where
+//      asked for, maxima and lowest argmaxes, and publishes them as tagged words, the offsets
+//      beside the sums;
 //   2. item s folds the S slice statistics of row s (rows s, s + S, ... when S is smaller
-//      than the row count) into the row's log2 normaliser L = hi + lo and publishes it;
+//      than the row count) into the row's log2 normaliser L = hi + lo and publishes it (sums
+//      against different offsets rescale by powers of two, so exactly);
 //   3. every item reads the normalisers and forms its slice's part of sum_v min(p_v, q_v)
 //      for each drafter: from the e_v kept in registers when the workgroup holds one item
 //      (one multiply, one min and one add per drafter logit), else from the logits again
@@ -69,7 +71,7 @@ struct TeamArgs {
   // ---- 128 bytes ----
   int64_t nvec;
   float c;
-  float o;             // integer-valued offset of every first exponent (launch_round)
+  float o;             // integer-valued common offset of the pipelined kernel's sums (launch_round)
   FastDiv divNsub;     // by nsub
   uint64_t* fail;      // set, with the call's tag, by the first wait that gives up
   uint32_t polls;      // polls before a wait gives up (0: every wait gives up at once)
@@ -131,27 +133,6 @@ __device__ inline uint64_t* norm_copy(const TeamArgs& A, int c, int rows) {
          (c - 1) * norm_copy_words(A.teams, rows);
 }
 
-// Row sums are taken against one fixed offset A.o, e_v = exp2(z_v c - A.o): in fp32's exponent range
-// a sum is as exact there as against the row's maximum, as long as it neither overflows nor sinks
-// towards the denormals, and the maxima, the offsets and the rescaling of every partial sum fall
-// away (a slice whose terms all underflow adds nothing to a row whose sum is in range). A row
-// whose sum is not within [2^-64, 2^100] (masked throughout, NaN, or of logits far from 0) is
-// retried: its folder publishes kRetry for its normaliser, every member then takes its slice's sum
-// again, against an offset from the slice's maximum, and publishes it with the sign bit set (a
-// first sum never has it), the maximum beside it, and the folder folds those. At the lower end
-// 2^17 terms below the normal range are 2^-45 of the sum; at the upper a row of 2^27 such slices
-// would still be finite.
-__device__ inline bool sum_in_range(float s) {
-  constexpr uint32_t kLo = (127u - 64u) << 23, kHi = (127u + 100u) << 23;
-  return __float_as_uint(s) - kLo <= kHi - kLo;
-}
-constexpr uint32_t kShifted = 0x80000000u;
-constexpr uint32_t kRetry = 0x7FC0FFFFu;  // a NaN; published NaNs are 0x7FC00000
-__device__ inline uint32_t plain_nan(float x) { return x != x ? 0x7FC00000u : __float_as_uint(x); }
-__device__ inline uint64_t word_of_bits(uint32_t x, uint32_t tag) {
-  return ((uint64_t)x << 32) | tag;
-}
-
 // A thread's offset for the exp2 sum of its logits of a row, m the largest of them: integer-valued
 // and at or above m c (exp_offset_of), so that sums against different offsets rescale exactly and
 // no exponent is positive. Held to [-2^29, 2^29], where differences of offsets fit an int32: beyond
@@ -164,18 +145,40 @@ __device__ inline float thread_offset(float m, float c) {
   return fminf(fmaxf(ceilf(fmaf(fabsf(mc), 0x1p-22f, mc)), (float)kNoOffset), 0x1p29f);
 }
 
-// Words of a row of a row set: S slice maxima (with an argmax, or where a sum is shifted; the
-// single-item kernel without an argmax: S slice offsets), S exp2 sums, S argmaxes. Each kind is contiguous, so that a fold's lanes read whole lines.
+// A thread's sum against its own offset has its exponents near 0 where they matter, so they are
+// rounded least, and nothing waits for a maximum. But maxima, offsets and rescaling are a seventh of
+// the pipelined kernel's instructions, which bound it. Against one common offset A.o they fall away
+// as long as every sum stays within fp32's range, with room (OWN = false below, without an argmax):
+// 16 queries x 64 drafters x 8 positions x 151936 bf16 logits 657 us, with own offsets 694; 64 x 8 x
+// 6 x 128256 216 and 222.
+// A wave in which a row's sums leave [2^-56, 2^96] (logits far from 0, masked or NaN) decides for
+// each row of the item by its threads' largest logits: A.o if all are in_common_range, else every
+// thread's own offset, the sums then marked by their sign bits; and it goes on so, without trying
+// A.o first, until an item needs it no more. A wave whose sums passed the test would decide for A.o
+// as well, so a result does not depend on what the wave did before. Where every wave decides so the
+// large calls take 11% longer than with own offsets throughout (the same two at logits 60 lower:
+// 775 and 695 us, 249 and 222); launch_t says which kernel a call takes.
+constexpr float kCommonLo = 0x1p-56f, kCommonHi = 0x1p96f;
+constexpr uint32_t kOwn = 0x80000000u;  // mark of a sum against its own offset
+// Largest logit m of up to 8 with a sum against `common` surely within [2^-60, 2^100]: m c - common
+// within [-60, 97].
+__device__ inline bool in_common_range(float m, float c, float common) {
+  return fabsf(fmaf(m, c, -(common + 18.5f))) <= 78.5f;
+}
+
+// Words of a row of a row set: S slice offsets (with an argmax: S slice maxima, from which the
+// offsets follow; with a common offset: those of marked sums only), S exp2 sums, S argmaxes. Each kind is contiguous, so that a fold's lanes read
+// whole lines.
 __device__ inline uint64_t* stat_row(const TeamArgs& A, int set, int r, int RM) {
   return A.stat + ((int64_t)set * RM + r) * A.S * 3;
 }
 
-// Log2 normaliser o + log2(sum) of row rr, o integer-valued (retry: the retry mark instead) as an
-// unevaluated sum hi + lo; lane c writes copy c. The sum's exponent is taken apart (exactly, also
+// Log2 normaliser o + log2(sum) of row rr, o integer-valued, as an unevaluated sum hi + lo; lane c
+// writes copy c. The sum's exponent is taken apart (exactly, also
 // from a large o): the logarithm then lies in [-1, 0), where its error is smallest.
 template <int D, int NC>
 __device__ __forceinline__ void publish_norm(const TeamArgs& A, int set, int rr, float o,
-                                             float sum, bool retry, uint32_t tt, int lane) {
+                                             float sum, uint32_t tt, int lane) {
   auto two_sum = [](float a, float b, float& err) {
     const float s = a + b, bb = s - a;
     err = (a - (s - bb)) + (b - bb);
@@ -187,35 +190,16 @@ __device__ __forceinline__ void publish_norm(const TeamArgs& A, int set, int rr,
   const float lo = e0 + e1;
   if (lane < NC) {
     uint64_t* cw = norm_copy(A, lane, D + 1) + ((int64_t)set * (D + 1) + rr) * 3;
-    put_word(cw, word_of_bits(retry ? kRetry : plain_nan(hi), tt));
-    put_word(cw + 1, word_of_bits(retry ? kRetry : plain_nan(lo), tt));
+    put_word(cw, word_of(hi, tt));
+    put_word(cw + 1, word_of(lo, tt));
   }
-}
-
-// The fold of a retried row: its S shifted sums, each against its own offset.
-template <int D>
-__device__ __forceinline__ void fold_retried(const TeamArgs& A, int set, int rr, uint32_t tag,
-                                             int lane) {
-  const uint64_t* base = stat_row(A, set, rr, D + 1);
-  float o = -INFINITY, sum = 0.0f;
-  bool lost = false;
-  for (int j = lane; j < A.S; j += 64) {
-    const uint64_t w = await_value(base + A.S + j, tag, A,
-                                   [](uint32_t x) { return (x & kShifted) == 0; });
-    const uint64_t mw = await_word(base + j, tag, A);
-    lost |= tainted(w) || tainted(mw);
-    lse2_combine(o, sum, exp_offset_of(word_f(mw), A.c),
-                 __uint_as_float((uint32_t)(w >> 32) & ~kShifted));
-  }
-  wave_lse(o, sum);
-  publish_norm<D, 1>(A, set, rr, o, sum, false, tag | taint_bits(__ballot(lost) != 0), lane);
 }
 
 // Fold of row rr of row set `set`: the S slice statistics, two slices per lane per pass
 // (lane j takes slices j, j + 64, ... in order), then the wave. Publishes the row's log2
 // normaliser as hi + lo (in NC copies) and its argmax; writes the argmax and agreement
 // outputs. The published words are tainted when any slice word was lost. OWN: every slice's sum is
-// against an offset of its own.
+// against an offset of its own, else marked ones are.
 template <int D, bool NEED_ARG, bool OWN, int NC = 1>
 __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int b, int k, int sub,
                                 uint32_t tag, int lane) {
@@ -225,13 +209,15 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
   float m = -INFINITY, sum = 0.0f;
   int idx = INT_MAX, o = kNoOffset;
   bool lost = false;
+  uint32_t marks = 0;
+  float plain = 0.0f;  // sum of the sums against A.o
   for (int j0 = 0; j0 < S; j0 += 128) {
     uint64_t w[2][3];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {  // issue every load of the pass before waiting on any
       const int j = j0 + lane + 64 * h;
       if (j < S) {
-        if (NEED_ARG || OWN) w[h][0] = get_word(base + j);
+        if (OWN) w[h][0] = get_word(base + j);
         w[h][1] = get_word(base + S + j);
         if (NEED_ARG) w[h][2] = get_word(base + 2 * S + j);
       }
@@ -240,7 +226,7 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
     for (int h = 0; h < 2; ++h) {
       const int j = j0 + lane + 64 * h;
       if (j < S) {
-        if (NEED_ARG || OWN) {
+        if (OWN) {
           if (tag_of(w[h][0]) != tag) w[h][0] = await_word(base + j, tag, A);
           lost |= tainted(w[h][0]);
         }
@@ -251,28 +237,36 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
         }
         if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + S + j, tag, A);
         lost |= tainted(w[h][1]);
-        if (OWN) {
+        if (!OWN && ((uint32_t)(w[h][1] >> 32) & kOwn) == 0) {
+          plain += word_f(w[h][1]);
+        } else {
+          if (!OWN) {
+            marks = kOwn;
+            w[h][0] = await_word(base + j, tag, A);
+            lost |= tainted(w[h][0]);
+          }
           const int oj = NEED_ARG ? (int)thread_offset(word_f(w[h][0]), A.c) : word_i(w[h][0]);
           const int on = max(o, oj);
-          sum = ldexpf(sum, o - on) + ldexpf(word_f(w[h][1]), oj - on);
+          sum = ldexpf(sum, o - on) + ldexpf(fabsf(word_f(w[h][1])), oj - on);
           o = on;
-        } else {
-          sum += word_f(w[h][1]);
         }
       }
     }
   }
   if (NEED_ARG) wave_max<true>(m, idx);
-  const bool any_lost = __ballot(lost) != 0;
-  const uint32_t tt = tag | taint_bits(any_lost);
   float ro = A.o;
-  if (OWN) {
-    const int on = wave_max_i(o);
+  if (OWN || __ballot(marks != 0) != 0) {
+    const int op = plain != 0.0f ? (int)A.o : kNoOffset;
+    const int on = wave_max_i(OWN ? o : max(o, op));
     sum = ldexpf(sum, o - on);
+    if (!OWN) sum += ldexpf(plain, op - on);
     ro = (float)on;
+  } else {
+    sum = plain;
   }
   sum = wave_sum_f(sum);
-  publish_norm<D, NC>(A, set, rr, ro, sum, !OWN && !any_lost && !sum_in_range(sum), tt, lane);
+  const uint32_t tt = tag | taint_bits(__ballot(lost) != 0);
+  publish_norm<D, NC>(A, set, rr, ro, sum, tt, lane);
   uint64_t* nw = A.norm + ((int64_t)set * RM + rr) * 3;
   if (lane != 0) return;
   if (NEED_ARG) {
@@ -320,21 +314,20 @@ __device__ inline ItemPos item_pos(const TeamArgs& A, uint32_t set, int slot, in
 // LDS of a team workgroup. Per-thread values of every row are stored transposed, [row][thread],
 // so that one 16-lane group reduces one row (group_read) instead of every wave reducing every
 // row on its own.
-constexpr uint32_t kWide = 0x80000000u;
 template <int D, bool NEED_ARG, bool SINGLE>
 struct TeamLds {
-  float xs[D + 1][kThreads];                    // per-thread exp2 sums (retry: max keys; SINGLE:
-                                                // later the min-sums of the drafters)
-  int xo[SINGLE ? D + 1 : 1][kThreads];         // SINGLE: the offsets that they are taken against
+  float xs[D + 1][kThreads];                    // per-thread exp2 sums (SINGLE: later the
+                                                // min-sums of the drafters)
+  int xo[D + 1][kThreads];                      // the offsets that they are taken against
   float xt[NEED_ARG ? D + 1 : 1][kThreads];     // per-thread maxima
   int xi[NEED_ARG ? D + 1 : 1][kThreads];       // per-thread argmax
   float xp[SINGLE ? 1 : D][kThreads];           // per-thread min-sums of each drafter
   int n[D + 1];     // SINGLE: the rows' rint(hi)
   float G[D];      // SINGLE: 2^(a_t - a_d)
-  float no[D + 1];  // retry: minus the slice offset, then (wide form) minus the row offset
+  float no[D + 1];  // minus the offset of the row's exponents (plain form: the target's only)
   float nw[D];     // plain: the exponent addend of drafter d
   float dl[D];     // wide: a_t - a_d
-  uint32_t form;   // 0: plain; kWide: wide; else the item's rows to retry (bit 2 r)
+  uint32_t wide;   // the min-sums take the wide form
   float F[D];      // factor of drafter d's group sum, 2^(a_t); SINGLE: 2^(a_d)
   uint32_t next;  // a row set of the team's coming items, posted by thread 0
   uint32_t taint;  // the item's normalisers include a lost word: its partials are tainted
@@ -423,11 +416,6 @@ __device__ __forceinline__ void mask_tail(const TeamArgs& A, const ItemPos& q,
   }
 }
 
-// The offset a slice is exponentiated against: exp_offset_of(m, c) when that is finite (an
-// integer-valued float, so that sums against different offsets rescale exactly), 0 for a slice
-// with no logit whose scaled value is finite (every e_v is then exp2(-inf) = 0).
-__device__ inline float exp_offset(float o) { return o != -INFINITY ? o : 0.0f; }
-
 // min of two values that are >= 0 or +NaN (0 * inf): the unsigned order of the bits is their
 // order and a NaN loses, as with fminf, without fminf's canonicalising of the operands.
 __device__ inline float min_pos(float a, float b) {
@@ -486,9 +474,10 @@ __device__ __forceinline__ float max_or_nan(const float (&z)[E]) {
   return m;
 }
 
-// ---- 1. per-thread statistics of every row of item q in one pass, to LDS: the exp2 sum (KEPT:
-// against the thread's own offset, and the e_v stay in x) and, with NEED_ARG, the max and its
-// lowest index ----
+// ---- 1. per-thread statistics of every row of item q in one pass, to LDS: the exp2 sum against the
+// thread's own offset (KEPT: the e_v stay in x) and, with NEED_ARG, the max and its lowest index.
+// An offset per thread needs no pass and no barrier before the sums, and keeps the exponents of
+// the terms that matter near 0, where they are rounded least, wherever the logits lie. ----
 template <int DT, int D, bool NEED_ARG, bool KEPT, typename L, typename X>
 __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q,
                                              typename Vec<DT>::Raw (&raw)[D + 1], X& x, L& sh,
@@ -515,12 +504,9 @@ __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q
       sh.xt[r][t] = m;
       sh.xi[r][t] = idx;
     }
-    float of = A.o;
-    if constexpr (KEPT) {
-      if (!NEED_ARG) m = max_or_nan(z);
-      of = thread_offset(m, A.c);
-      sh.xo[r][t] = (int)of;
-    }
+    if (!NEED_ARG) m = max_or_nan(z);
+    const float of = thread_offset(m, A.c);
+    sh.xo[r][t] = (int)of;
     float v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -529,6 +515,65 @@ __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q
     }
     sh.xs[r][t] = sum_elems(v);
   }
+}
+
+// min and max of three that are NaN when one of them is
+__device__ __forceinline__ float minimum3(float a, float b, float c) {
+  float r;
+  asm("v_minimum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// The same against the common offset where that fits (own: the wave's last item needed its own
+// offsets; updated).
+template <int DT, int D, typename L>
+__device__ __forceinline__ void thread_stats_common(const TeamArgs& A, const ItemPos& q,
+                                             typename Vec<DT>::Raw (&raw)[D + 1], L& sh, int t,
+                                             bool& own) {
+  constexpr int E = Vec<DT>::kElems;
+  const bool past = q.vi >= A.nvec;  // no logit of any row
+  if (!own) {
+    float lo = 1.0f, hi = 1.0f, prev = 1.0f;
+#pragma unroll
+    for (int r = 0; r <= D; ++r) {
+      if (r > q.n) continue;
+      launder(raw[r]);
+      float z[E], v[E];
+      Vec<DT>::unpack(raw[r], z);
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, -A.o));
+      const float s = sum_elems(v);
+      sh.xs[r][t] = s;
+      if (r & 1) {  // two rows at a time
+        lo = minimum3(lo, prev, s);
+        hi = maximum3(hi, prev, s);
+        prev = 1.0f;
+      } else {
+        prev = s;
+      }
+    }
+    lo = minimum3(lo, prev, prev);
+    hi = maximum3(hi, prev, prev);
+    own = __ballot(!past && !(lo >= kCommonLo && hi <= kCommonHi)) != 0;
+    if (!own) return;
+  }
+  bool needed = false;
+#pragma unroll
+  for (int r = 0; r <= D; ++r) {
+    if (r > q.n) continue;
+    launder(raw[r]);
+    float z[E], v[E];
+    Vec<DT>::unpack(raw[r], z);
+    const float m = max_or_nan(z);
+    const bool common = __ballot(!past && !in_common_range(m, A.c, A.o)) == 0;
+    needed |= !common;
+    const float of = common ? A.o : thread_offset(m, A.c);
+    sh.xo[r][t] = (int)of;
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, -of));
+    sh.xs[r][t] = common ? sum_elems(v) : -fabsf(sum_elems(v));
+  }
+  own = needed;
 }
 
 // ---- 2. row reductions: 16-lane group gi reduces row gi of the LDS rows (groups past the last
@@ -548,54 +593,91 @@ __device__ __forceinline__ void group_argmax(const L& sh, int n, int gi, int gl,
   for (int u = 1; u < 16; ++u) argmax_combine(m, idx, v[u], iv[u]);
   row16_argmax(m, idx);
 }
-template <typename L>
-__device__ __forceinline__ float group_sum(const L& sh, int n, int gi, int gl) {
-  float v[16];
-  group_read(&sh.xs[min(gi, n)][0], gl, v);
-  return row16_sum(sum16(v));
-}
-
 // Slot s's duty index for an item whose duties start at slot rot: duties are numbered from
 // rot on, so that the row and alpha folds move round the team from item to item instead of
 // falling on the same few members every time (the team goes at its slowest member's pace).
 __device__ inline int duty_index(int s, int rot, int S) { return s >= rot ? s - rot : s - rot + S; }
 
-// Reduces and publishes the slice statistics of item q as tagged words (OWN: the threads' sums are
-// against offsets of their own, and the slice's sum is published against the largest of them,
-// beside it; with an argmax that offset follows from the maximum).
-template <bool NEED_ARG, bool OWN, typename L>
+// Reduces and publishes the slice statistics of item q as tagged words: the slice's sum is taken
+// against the largest of its threads' offsets and published beside it, the offset before the sum
+// (a fold that finds a marked sum then finds its offset on the way).
+template <bool NEED_ARG, typename L>
 __device__ __forceinline__ void publish_stats(const TeamArgs& A, const ItemPos& q, uint32_t tag,
                                               int RM, L& sh, int gi, int gl) {
   float m = 0.0f;
   int idx = 0;
   if (NEED_ARG) group_argmax(sh, q.n, gi, gl, m, idx);
-  float s;
-  int o = 0;
-  if constexpr (OWN) {
-    const int r = min(gi, q.n);
-    int ov[16];
-    group_read(&sh.xo[r][0], gl, ov);
-    o = ov[0];
+  const int r = min(gi, q.n);
+  int ov[16];
+  group_read(&sh.xo[r][0], gl, ov);
+  int o = ov[0];
 #pragma unroll
-    for (int u = 1; u < 16; ++u) o = max(o, ov[u]);
-    o = row16_max(o);
-    float v[16];
-    group_read(&sh.xs[r][0], gl, v);
+  for (int u = 1; u < 16; ++u) o = max(o, ov[u]);
+  o = row16_max(o);
+  float v[16];
+  group_read(&sh.xs[r][0], gl, v);
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = ldexpf(v[u], ov[u] - o);
-    s = row16_sum(sum16(v));
-  } else {
-    s = fabsf(group_sum(sh, q.n, gi, gl));  // (a NaN's sign)
-  }
+  for (int u = 0; u < 16; ++u) v[u] = ldexpf(v[u], ov[u] - o);  // exact, or to the denormals
+  const float s = row16_sum(sum16(v));
   if (gl != 0 || gi > q.n) return;
   uint64_t* wp = stat_row(A, q.set, gi, RM) + q.s;
-  if (NEED_ARG) {
-    put_word(wp, word_of(m, tag));
-    put_word(wp + 2 * A.S, word_of(idx, tag));
-  } else if (OWN) {
-    put_word(wp, word_of(o, tag));
-  }
+  put_word(wp, NEED_ARG ? word_of(m, tag) : word_of(o, tag));
   put_word(wp + A.S, word_of(s, tag));
+  if (NEED_ARG) put_word(wp + 2 * A.S, word_of(idx, tag));
+}
+
+// The same where waves are against the common offset (without an argmax).
+template <typename L>
+__device__ __forceinline__ void publish_stats_common(const TeamArgs& A, const ItemPos& q,
+                                                     uint32_t tag, int RM, L& sh, int gi, int gl) {
+  const int r = min(gi, q.n);
+  typedef float F4 __attribute__((ext_vector_type(4)));
+  typedef int I4 __attribute__((ext_vector_type(4)));
+  // this lane's values of wave i: sums and offsets (group_read's order)
+  auto sums = [&](int i) { return *reinterpret_cast<const F4*>(&sh.xs[r][64 * i + 4 * gl]); };
+  auto offsets = [&](int i) { return *reinterpret_cast<const I4*>(&sh.xo[r][64 * i + 4 * gl]); };
+  auto marked = [&](float x) { return (__float_as_uint(x) & kOwn) != 0; };
+  int o = kNoOffset;
+  uint32_t mark = 0;
+  float c[4], first[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const F4 x = sums(i);
+    first[i] = x[0];  // the marks of a wave's sums of a row are alike
+    c[i] = (x[0] + x[1]) + (x[2] + x[3]);
+  }
+  if (__ballot(marked(first[0]) || marked(first[1]) || marked(first[2]) || marked(first[3])) != 0) {
+    // (some row of this wave's.) Offset of an unmarked sum: A.o (the one in LDS is an earlier
+    // item's); it is 0 only past the row's end
+    auto offset = [&](const F4& x, const I4& y, int k) {
+      if (marked(x[0])) return y[k];
+      return (x[0] + x[1]) + (x[2] + x[3]) == 0.0f ? kNoOffset : (int)A.o;
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const F4 x = sums(i);
+      const I4 y = offsets(i);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o = max(o, offset(x, y, k));
+    }
+    o = row16_max(o);
+    mark = o != (int)A.o ? kOwn : 0u;
+    asm volatile("" ::: "memory");  // read again rather than hold 32 registers
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const F4 x = sums(i);
+      const I4 y = offsets(i);
+      float e[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) e[k] = ldexpf(fabsf(x[k]), offset(x, y, k) - o);  // exact, or far below
+      c[i] = (e[0] + e[1]) + (e[2] + e[3]);
+    }
+  }
+  const float s = row16_sum((c[0] + c[1]) + (c[2] + c[3]));
+  if (gl != 0 || gi > q.n) return;
+  uint64_t* wp = stat_row(A, q.set, gi, RM) + q.s;
+  if (mark) put_word(wp, word_of(o, tag));
+  put_word(wp + A.S, word_of(__uint_as_float((__float_as_uint(s) & ~kOwn) | mark), tag));
 }
 
 // ---- 4. fold duty: rows i, i + S, ... of the row set (i = the slot's duty index for the
@@ -609,124 +691,70 @@ __device__ __forceinline__ void fold_item(const TeamArgs& A, const ItemPos& q, u
 }
 
 // ---- 5. normalisers L = hi + lo (the duty wave; a barrier follows): lanes 2r and 2r + 1 wait for
-// row r's hi and lo. A row with no finite logit folds to hi = -inf, lo = NaN: it has no
-// distribution, which makes alpha NaN for that drafter, or for every drafter of that target.
-// Lane 2r forms a_r = (o_r - hi_r) - lo_r, o_r = rint(hi_r) with KEPT and in the wide form (after a
-// retry, AGAIN, every normaliser final), else A.o, the offset of the row's exponents, and for a
-// drafter row the constants of its min-sum. KEPT (6'): o_r, G = 2^(a_t - a_d) and F = 2^(a_d). Else
-// (6): exponent addend nw = -A.o - (a_t - a_d), or the difference itself in the wide form, and
-// F = 2^(a_t). Differences of the a_r are taken part by part, so that they lose nothing to a large
-// hi. ----
-template <int D, bool KEPT, bool AGAIN, typename L>
+// row r's hi and lo; lane 2r forms a_r = (o_r - hi_r) - lo_r, o_r an integer-valued offset for the
+// row's exponents, and for a drafter row the constants of its min-sum to LDS. A row with no finite
+// logit folds to hi = -inf, lo = NaN, so its a is NaN: it has no distribution, and F is NaN whenever
+// a_t or a_d is, which makes that drafter's alpha NaN in every form. Differences of the a_r are
+// taken part by part, so that they lose nothing to a large hi.
+// KEPT (6'): o_r = rint(hi_r); G = 2^(a_t - a_d) and F = 2^(a_d).
+// Else (6), plain form: one o for all rows, half the target's normaliser. An exponent of a term that
+// matters is then about as far from 0 as the addend nw = -o - (a_t - a_d) that holds o and the
+// difference in one float, and both are rounded alike, at 2^-24 of half of |hi|. (Rows more than 32
+// apart: the whole of it, which leaves |nw| = |hi_d|.) Where either is large (|hi_t| > 128,
+// |nw| > 64: 2^-19 of a term) the wide form: o_r = rint(hi_r), and the difference is subtracted
+// in an operation of its own. F = 2^(a_t). ----
+template <int D, bool KEPT, typename L>
 __device__ __forceinline__ void await_norms(const TeamArgs& A, const ItemPos& q, uint32_t tag,
                                             L& sh, int lane) {
   float h = 0.0f;
   bool lost = false;
   if (lane < 2 * (q.n + 1)) {
     constexpr int NC = KEPT ? kNormCopies : 1;  // the single-item kernel's fold writes copies
-    const uint64_t* p = norm_copy(A, q.s & (NC - 1), D + 1) +
-                        ((int64_t)q.set * (D + 1) + (lane >> 1)) * 3 + (lane & 1);
-    const uint64_t w = AGAIN ? await_value(p, tag, A, [](uint32_t x) { return x == kRetry; })
-                             : await_word(p, tag, A);
+    const uint64_t w =
+        await_word(norm_copy(A, q.s & (NC - 1), D + 1) +
+                       ((int64_t)q.set * (D + 1) + (lane >> 1)) * 3 + (lane & 1),
+                   tag, A);
     h = word_f(w);
     lost = tainted(w);
   }
   const bool any_lost = __ballot(lost) != 0;
   if (lane == 0) sh.taint = taint_bits(any_lost);
-  const bool row = !(lane & 1) && lane < 2 * (q.n + 1);
-  const uint64_t retry = __ballot(row && __float_as_uint(h) == kRetry);
-  if (!KEPT && lane == 0) sh.form = AGAIN ? kWide : (uint32_t)retry;
   const float lo = dpp_f<0xB1>(h);  // lane 2r: the lo of row r, from lane 2r + 1
-  float o = A.o;
-  if ((KEPT || AGAIN) && row) {
-    o = rintf(h);
-    if (KEPT) sh.n[lane >> 1] = cvt_i32_sat(o);
-    else sh.no[lane >> 1] = fabsf(o) < INFINITY ? -o : 0.0f;
-  }
-  const float x = o - h;
-  const float xt = lane_f(x, 0), lot = lane_f(lo, 0);
-  if (row && lane >= 2) {
-    const int d = (lane >> 1) - 1;
-    const float at = xt - lot, a = x - lo;
-    const bool undefined = at != at || a != a;
-    const float diff = (xt - x) - (lot - lo);  // a_t - a_d
-    if (KEPT) {
-      sh.G[d] = __builtin_amdgcn_exp2f(diff);
-      sh.F[d] = undefined ? NAN : __builtin_amdgcn_exp2f(a);
-    } else {
-      sh.nw[d] = -A.o - diff;
-      if (AGAIN) sh.dl[d] = diff;
-      sh.F[d] = undefined ? NAN : exp2_split(xt, lot);
-    }
-  }
-}
-
-// ---- 5'. retry of the rows of item q whose first sum was out of range (form: bit 2 r for row
-// r, uniform): their slice sums again, against the offset of the slice's maximum (exp_offset_of:
-// integer-valued, at or above m c; -inf, and a sum of 0, for a slice with no logit whose scaled
-// value is finite), published with the maximum; then the folds, and all normalisers. The whole
-// workgroup calls this after a barrier, and it ends with one. Every member of the team comes
-// here for the same item, before it waits for any word of a later one, so the waits end. The
-// logits come from memory again (rare rows are not worth registers). ----
-template <int DT, int D, typename L>
-__device__ __forceinline__ void retry_item(const TeamArgs& A, const ItemPos& q, uint32_t form,
-                                           uint32_t tag, L& sh, int t, int first, int rot) {
-  using Vt = Vec<DT>;
-  constexpr int E = Vt::kElems;
-  const int lane = t & 63, wv = t >> 6, gi = t >> 4, gl = t & 15;
-  const bool rows = wv * 4 <= q.n;
-  const bool mine = rows && gi <= q.n && gl == 0 && ((form >> (2 * min(gi, D))) & 1u) != 0;
-  auto load = [&](int r, float (&z)[E]) {
-    const int row = r == 0 ? 0 : q.sub * D + r;
-    const char* p = static_cast<const char*>(A.rows.ptr[row]) +
-                    ((int64_t)q.b * A.rows.sb[row] + (int64_t)q.k * A.rows.sk[row]) * Vt::kBytes;
-    if (q.vi < A.nvec) Vt::load(p, q.vi, A.V, z);
-    else Vt::unpack(Vt::neg_raw(), z);
+  const bool row = !(lane & 1) && lane < 2 * (q.n + 1), drafter = row && lane >= 2;
+  const int d = (lane >> 1) - 1;
+  const float ht = lane_f(h, 0), lot = lane_f(lo, 0);
+  const bool undefined = ht + lot != ht + lot || h + lo != h + lo;
+  const bool apart = !KEPT && __ballot(drafter && fabsf(h - ht) > 32.0f) != 0;
+  float o = KEPT ? rintf(h) : rintf(apart ? ht : 0.5f * ht);
+  // a_t - a_d for this lane's o
+  auto diff = [&]() {
+    const float x = o - h;
+    return (lane_f(x, 0) - x) - (lot - lo);
   };
-  for (int r = 0; r <= q.n; ++r) {
-    if (((form >> (2 * r)) & 1u) == 0) continue;
-    float z[E];
-    load(r, z);
-    float m = -INFINITY;
-#pragma unroll
-    for (int e = 0; e < E; ++e) m = fmaxf(m, z[e]);
-    sh.xs[r][t] = __int_as_float(fkey(m));  // integer key: the group max needs no NaN care
-  }
-  __syncthreads();
-  float m = 0.0f;
-  if (rows) {
-    int kv[16];
-    group_read(reinterpret_cast<const int*>(&sh.xs[min(gi, q.n)][0]), gl, kv);
-    int k = kv[0];
-#pragma unroll
-    for (int u = 1; u < 16; ++u) k = max(k, kv[u]);
-    m = fkey_inv(row16_max(k));
-    if (gl == 0 && gi <= q.n) sh.no[gi] = -exp_offset(exp_offset_of(m, A.c));
-  }
-  __syncthreads();
-  for (int r = 0; r <= q.n; ++r) {
-    if (((form >> (2 * r)) & 1u) == 0) continue;
-    float z[E];
-    load(r, z);
-    const float no = sh.no[r];
-#pragma unroll
-    for (int e = 0; e < E; ++e) z[e] = __builtin_amdgcn_exp2f(fmaf(z[e], A.c, no));
-    sh.xs[r][t] = sum_elems(z);
-  }
-  __syncthreads();
-  if (rows) {
-    const float s = group_sum(sh, q.n, gi, gl);
-    if (mine) {
-      uint64_t* wp = stat_row(A, q.set, gi, D + 1) + q.s;
-      put_word(wp, word_of(m, tag));
-      put_word(wp + A.S, word_of_bits(__float_as_uint(s) | kShifted, tag));
+  float df = diff();
+  if (!KEPT) {
+    const float nw = ((ht - o) - h) + (lot - lo);  // -o - df, without df's rounding where rows lie far apart
+    const bool wide =
+        __ballot((drafter && !undefined && fabsf(nw) > 64.0f) || (lane == 0 && fabsf(ht) > 128.0f)) != 0;
+    if (lane == 0) sh.wide = wide;
+    if (wide) {
+      o = rintf(h);
+      df = diff();
+    }
+    if (drafter) {
+      sh.nw[d] = nw;
+      sh.dl[d] = df;
+    }
+    if (row) sh.no[lane >> 1] = fabsf(o) < INFINITY ? -o : 0.0f;
+    const float f = exp2_split(lane_f(o, 0) - ht, lot);
+    if (drafter) sh.F[d] = undefined ? NAN : f;
+  } else {
+    if (row) sh.n[lane >> 1] = cvt_i32_sat(o);
+    if (drafter) {
+      sh.G[d] = __builtin_amdgcn_exp2f(df);
+      sh.F[d] = undefined ? NAN : __builtin_amdgcn_exp2f((o - h) - lo);
     }
   }
-  const int order = (wv + kWaves - first) % kWaves;
-  for (int rr = duty_index(q.s, rot, A.S) + order * A.S; rr <= q.n; rr += kWaves * A.S)
-    if ((form >> (2 * rr)) & 1u) fold_retried<D>(A, q.set, rr, tag, lane);
-  if (wv == first) await_norms<D, false, true>(A, q, tag, sh, lane);
-  __syncthreads();
 }
 
 // ---- 6'. per-thread min-sums from kept e_v: with b_r the thread's offset of row r less the
@@ -757,7 +785,7 @@ __device__ __forceinline__ void thread_minsums_kept(const ItemPos& q,
 
 // ---- 6. per-thread min-sums, from the logits again: with u_v = z_t,v c - o_t and
 // w_v = z_d,v c - o_d, p_v = 2^(u_v + a_t) and q_v = 2^(w_v + a_d), so
-// min(p_v, q_v) = 2^(a_t) 2^min(u_v, w_v - (a_t - a_d)), and in the plain form (both o = A.o)
+// min(p_v, q_v) = 2^(a_t) 2^min(u_v, w_v - (a_t - a_d)), and in the plain form (one o)
 // w_v - (a_t - a_d) is one fma z_d,v c + nw_d; one fma, one min, one exp2 and one add per
 // drafter logit. The factor 2^(a_t) is applied to the group sum. Identical rows give nw_d = -o,
 // so both operands agree bitwise ----
@@ -769,7 +797,7 @@ __device__ __forceinline__ void thread_minsums_form(const TeamArgs& A, const Ite
   float u[E];
   launder(raw[0]);
   Vec<DT>::unpack(raw[0], u);
-  const float nt = WIDE ? sh.no[0] : -A.o;
+  const float nt = sh.no[0];
 #pragma unroll
   for (int e = 0; e < E; ++e) u[e] = fmaf(u[e], A.c, nt);
 #pragma unroll
@@ -802,7 +830,7 @@ template <int DT, int D, typename L>
 __device__ __forceinline__ void thread_minsums(const TeamArgs& A, const ItemPos& q,
                                                typename Vec<DT>::Raw (&raw)[D + 1], L& sh,
                                                int t) {
-  if (sh.form == 0) thread_minsums_form<DT, D, false>(A, q, raw, sh, t);
+  if (sh.wide == 0) thread_minsums_form<DT, D, false>(A, q, raw, sh, t);
   else thread_minsums_form<DT, D, true>(A, q, raw, sh, t);
 }
 
@@ -927,18 +955,31 @@ __device__ __forceinline__ void finish(const TeamArgs& A, uint32_t tag, bool cou
 // the statistics of the next. Two raw buffers (not three, with the next loads issued before
 // the statistics) keep the kernel within 128 VGPRs, so four workgroups share a CU: 3-4% faster
 // on every large workload than three workgroups with three buffers.
-// SINGLE (alpha kernels only): every team has exactly one item, so nothing is pipelined, the
+// COMMON (pipelined, without an argmax): sums against one common offset where they fit it.
+// SINGLE: every team has exactly one item, so nothing is pipelined, the
 // e_v stay in registers and drafters at a constant distance are addressed without the table.
 // With an argmax as well the pipelined kernel runs 3 workgroups per CU: held to the 128 registers of
 // a fourth it spills 140 bytes and runs 58 us instead of 45 (13 queries x 5 drafters x 7 positions x
 // 50257 fp16 logits).
-template <int DT, int D, bool NEED_ARG, bool SINGLE>
+template <int DT, int D, bool NEED_ARG, bool SINGLE, bool COMMON>
 __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team_kernel(TeamArgs A) {
   using Raw = typename Vec<DT>::Raw;
   constexpr int RM = D + 1;
   __shared__ TeamLds<D, NEED_ARG, SINGLE> sh;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int gi = t >> 4, gl = t & 15;  // 16-lane group gi reduces row gi; gl: lane in it
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int t, lane, gi, gl;  // 16-lane group gi reduces row gi; gl: lane in it
+  // The thread's indices afresh: taken from an opaque copy, so that the pipelined kernel's many LDS
+  // and word addresses are formed where they are used instead of being kept across its loop, where
+  // they would not fit in registers (a spilled one comes back by a load that waits for the next
+  // item's logits).
+  auto reindex = [&]() __attribute__((always_inline)) {
+    t = threadIdx.x;
+    if (!SINGLE) asm volatile("" : "+v"(t));
+    lane = t & 63;
+    gi = t >> 4;
+    gl = t & 15;
+  };
+  reindex();
   const int S = A.S;
   // every scalar the first loads depend on, requested in one round at entry (otherwise each
   // is loaded just before its first use, one scalar-cache round trip apiece); the pipelined
@@ -984,14 +1025,20 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     return (int)(x - fdiv(x, A.divS) * (uint32_t)S);
   };
 
+  bool own = false;  // COMMON: this wave's last item needed offsets of its own
   // statistics of item q from raw, published
   auto stats = [&](const ItemPos& q, Raw (&raw)[RM]) __attribute__((always_inline)) {
     __builtin_amdgcn_s_setprio(kCritPrio);
+    reindex();
     mask_tail<DT, D>(A, q, raw);
-    thread_stats<DT, D, NEED_ARG, false>(A, q, raw, sh, sh, t);
+    if constexpr (COMMON) thread_stats_common<DT, D>(A, q, raw, sh, t, own);
+    else thread_stats<DT, D, NEED_ARG, false>(A, q, raw, sh, sh, t);
     __syncthreads();
-    if (wv * 4 <= q.n)  // this wave holds the group of a row
-      publish_stats<NEED_ARG, false>(A, q, tag, RM, sh, gi, gl);
+    reindex();
+    if (wv * 4 <= q.n) {  // this wave holds the group of a row
+      if constexpr (COMMON) publish_stats_common(A, q, tag, RM, sh, gi, gl);
+      else publish_stats<NEED_ARG>(A, q, tag, RM, sh, gi, gl);
+    }
     __builtin_amdgcn_s_setprio(0);
   };
   // the item's slice partials to the workspace (after a barrier), as tagged words
@@ -1045,7 +1092,7 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     mask_tail<DT, D>(A, q, R0);
     thread_stats<DT, D, NEED_ARG, true>(A, q, R0, x, sh, t);
     __syncthreads();
-    if (wv * 4 <= q.n) publish_stats<NEED_ARG, true>(A, q, tag, RM, sh, gi, gl);
+    if (wv * 4 <= q.n) publish_stats<NEED_ARG>(A, q, tag, RM, sh, gi, gl);
     fold_item<D, NEED_ARG, true, kNormCopies>(A, q, tag, lane, wv, 0);
     __builtin_amdgcn_s_setprio(0);
     // with one item per workgroup the leader counts its team once it has folded row 0 (every
@@ -1053,7 +1100,7 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     // then overlaps the normaliser wait instead of following the learner step or the alpha
     // folds. (The fold duties start at wave 0, whose thread 0 counts.)
     if (leader && t == 0) count_team(A, tag, teams);
-    if (wv == 0) await_norms<D, true, false>(A, q, tag, sh, lane);
+    if (wv == 0) await_norms<D, true>(A, q, tag, sh, lane);
     __syncthreads();
     thread_minsums_kept<DT, D>(q, x, sh, t);
     __syncthreads();
@@ -1064,6 +1111,7 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     finish(A, tag, false, teams, sh, t);
     return;
   }
+  uint32_t pset = nsets;  // the team's previous item, whose alpha is still to be folded
   uint32_t set1 = successor(set);
   uint32_t set2 = successor(set1);  // items 0-2 lie in fixed blocks: never kClaim
   fetch_item<DT, D>(A, item_pos(A, min(set1, nsets - 1), slot, D), set1 < nsets, sh,
@@ -1076,7 +1124,6 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
   // barriers around the min-sums); after it every wave has published its rows
   __syncthreads();
 
-  uint32_t pset = nsets;  // the team's previous item, whose alpha is still to be folded
   // iteration j: rc holds item j (statistics published) and then receives item j + 2, rn
   // holds item j + 1 (loaded). Returns false once the team has no item j + 1.
   auto iter = [&](int j, Raw (&rc)[RM], Raw (&rn)[RM])
@@ -1084,14 +1131,14 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     const ItemPos q = item_pos(A, set, slot, D);
     // the leader's claim of item j + 3 goes out before the fold and is posted after it, so
     // waiting for its result waits for nothing else; the duty wave, which folds, claims
-    // (the argmax-only kernel, whose folds are short, claims on thread 0)
     const uint32_t set3 = successor(set2);  // item j + 3, unless it is to be claimed
     const bool claiming = set3 == kClaim && leader && wv == kDutyWave && lane == 0;
     uint32_t cv = 0;
     if (claiming)
       cv = __hip_atomic_fetch_add(A.next_set, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_s_setprio(kFoldPrio);
-    fold_item<D, NEED_ARG, false>(A, q, tag, lane, wv, kDutyWave, rotation(set, 0));
+    reindex();
+    fold_item<D, NEED_ARG, !COMMON>(A, q, tag, lane, wv, kDutyWave, rotation(set, 0));
     __builtin_amdgcn_s_setprio(0);
     if (claiming)
       put_word(mbox + ((j + 3) & 3),
@@ -1099,13 +1146,13 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
     if (set1 < nsets) stats(item_pos(A, set1, slot, D), rn);
     else __syncthreads();  // the previous item's constants in LDS are no longer read
     if (set3 == kClaim && t == 0) sh.next = await_mbox(mbox + ((j + 3) & 3), j + 3, tag, A, nsets);
-    if (wv == kDutyWave) await_norms<D, false, false>(A, q, tag, sh, lane);
+    reindex();
+    if (wv == kDutyWave) await_norms<D, false>(A, q, tag, sh, lane);
     __syncthreads();
-    const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.form);
-    if (form)
-      retry_item<DT, D>(A, q, form, tag, sh, t, kDutyWave, rotation(set, 0));
+    reindex();
     thread_minsums<DT, D>(A, q, rc, sh, t);
     __syncthreads();
+    reindex();
     store_partials(q);
     fetch_item<DT, D>(A, item_pos(A, min(set2, nsets - 1), slot, D), set2 < nsets, sh, rc);
     // alpha of the previous item, whose partials were stored an iteration ago; its polls
@@ -1141,7 +1188,7 @@ std::atomic<uint32_t> g_wait_polls{kDefaultPolls};
 uint32_t wait_polls() { return g_wait_polls.load(std::memory_order_relaxed); }
 
 // Workgroups of the team kernel the current device holds at once.
-template <int DT, int D, bool NA, bool SG>
+template <int DT, int D, bool NA, bool SG, bool CO>
 int capacity_t() {
   static std::atomic<int> cached[64];  // per device; 0 = not yet known
   int dev = 0;
@@ -1149,7 +1196,7 @@ int capacity_t() {
   int v = cached[dev].load(std::memory_order_relaxed);
   if (v > 0) return v;
   int per_cu = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, hs_team_kernel<DT, D, NA, SG>,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, hs_team_kernel<DT, D, NA, SG, CO>,
                                                    kThreads, 0) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
@@ -1164,11 +1211,16 @@ int capacity_t() {
 template <int DT, int D, bool NA>
 int launch_t(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* learned) {
   const int64_t sets = g.items / g.S;
-  const bool single = capacity_t<DT, D, NA, true>() / g.S >= sets;
+  const bool single = capacity_t<DT, D, NA, true, false>() / g.S >= sets;
+  // The common offset's range is 152 binary orders, which at a low temperature the rows' maxima no
+  // longer fit: T = 0.4, 0.3, 0.2 and 0.1 with the common offset 217, 221, 233 and 254 us, with own
+  // offsets 222, 222, 223 and 228 (64 queries x 8 drafters x 6 positions x 128256 bf16 logits);
+  // 51, 51, 60 and 60 us against 51 throughout (64 x 4 x 4 x 32000 fp32).
+  constexpr float kCommonScale = 5.0f;  // log2(e) / T: T of about 0.29
+  const bool common = !NA && !single && A.c <= kCommonScale;
+  const int cap = common ? capacity_t<DT, D, NA, false, !NA>() : capacity_t<DT, D, NA, false, false>();
   const int64_t teams =
-      single ? sets
-             : std::min<int64_t>({capacity_t<DT, D, NA, false>() / g.S, sets,
-                                  (int64_t)kMaxTeams});
+      single ? sets : std::min<int64_t>({cap / g.S, sets, (int64_t)kMaxTeams});
   if (teams <= 0) return HS_ERR_LIMIT;
   const int64_t P = teams * g.S;
   if (A.learn) {
@@ -1178,8 +1230,9 @@ int launch_t(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* learned) {
   }
   *learned = A.learn != 0;
   A.teams = (int)teams;
-  if (single) hs_team_kernel<DT, D, NA, true><<<(unsigned)P, kThreads, 0, stream>>>(A);
-  else hs_team_kernel<DT, D, NA, false><<<(unsigned)P, kThreads, 0, stream>>>(A);
+  if (single) hs_team_kernel<DT, D, NA, true, false><<<(unsigned)P, kThreads, 0, stream>>>(A);
+  else if (common) hs_team_kernel<DT, D, NA, false, !NA><<<(unsigned)P, kThreads, 0, stream>>>(A);
+  else hs_team_kernel<DT, D, NA, false, false><<<(unsigned)P, kThreads, 0, stream>>>(A);
   return HS_OK;
 }
 
@@ -1205,9 +1258,10 @@ int dispatch(const TeamGeom& g, bool na, Args&&... args) {
 }
 
 template <int DT, int D, bool NA>
-struct Capacity {  // the smaller of the two kernels' (a team must fit in either)
+struct Capacity {  // the smallest of the kernels' (a team must fit in any)
   static int run() {
-    return std::min(capacity_t<DT, D, NA, false>(), capacity_t<DT, D, NA, true>());
+    return std::min({capacity_t<DT, D, NA, false, !NA>(), capacity_t<DT, D, NA, false, false>(),
+                     capacity_t<DT, D, NA, true, false>()});
   }
 };
 template <int DT, int D, bool NA>
