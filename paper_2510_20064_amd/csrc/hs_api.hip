@@ -116,7 +116,7 @@ int validate_eval(const EvalReq& q, hs::TeamGeom* g, hs::RowTable* rows) {
 }
 
 // The one check that asks the device, made after every host-side check: a team of S
-// workgroups must fit on the device at once (without alpha nothing waits for a team).
+// workgroups must fit on the device at once (without alpha another kernel takes what does not).
 int check_capacity(const EvalReq& q, const hs::TeamGeom& g) {
   if (!q.alpha) return HS_OK;
   const int cap = hs::team_capacity(g, q.agree || q.argmax_t || q.argmax_d);

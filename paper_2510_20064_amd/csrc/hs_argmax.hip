@@ -6,19 +6,15 @@
 //   2. the wave that arrives last at a group folds the group's rows, reads the one vector that
 //      holds each row's maximum for the element, and writes the argmaxes and agreements.
 // Bound by HBM: 64 queries x 8 drafters x 6 positions x 128256 bf16 logits in 142 us (6.2 TB/s; the
-// card streams 7.0). The argmax variant of the team kernel, whose members waited for each other's
-// words between the loads of one item and the next, took 193 us.
-#include <algorithm>
-
+// card streams 7.0). The argmax variant of the team kernel, whose members wait for each other's
+// words between the loads of one item and the next, takes 189 us; it takes the calls with few items
+// (launch_team_argmax).
 #include "hs_exchange.h"
 
 namespace hs {
 namespace {
 
-constexpr int kStep = 8;  // 16-byte loads of a unit per lane
-// Waves of a launch, when there are units enough: the device holds 4096 to 6144 of them at once, and
-// more and shorter spans only add arrivals (142 us with 4096 and 6144, 153 with 12288).
-constexpr int64_t kMinWaves = 4096;
+constexpr int kStep = kArgmaxStep;
 // Polls of an adder for its count to be opened (the opening wave comes first in dispatch order and
 // opens while its own first loads fly, so an adder hardly ever meets a count that is not open).
 constexpr uint32_t kOpenPolls = 1u << 10;
@@ -244,13 +240,12 @@ int launch_argmax(const TeamGeom& g, const RowTable& rows, uint8_t* agree, int32
   A.G = g.G;
   A.V = g.V;
   A.nvec = g.nvec;
-  const int64_t unit = 64 * kStep;
-  A.S = (int)((g.nvec + unit - 1) / unit);
-  const int64_t per_group = (int64_t)(g.N + 1) * A.S;
-  A.total = (int)(g.G * per_group);
-  A.span = (int)std::max<int64_t>((A.total + kMinWaves - 1) / kMinWaves, 1);
-  A.pieces = (A.S + A.span - 2) / A.span + 1;
-  A.div_group = make_fastdiv((uint32_t)per_group);
+  const ArgmaxPlan p = argmax_plan(g);
+  A.S = p.S;
+  A.total = (int)p.total;
+  A.span = (int)p.span;
+  A.pieces = (int)p.pieces;
+  A.div_group = make_fastdiv((uint32_t)p.per_group);
   A.divS = make_fastdiv((uint32_t)A.S);
   A.divK = make_fastdiv((uint32_t)g.K);
   A.div_span = make_fastdiv((uint32_t)A.span);

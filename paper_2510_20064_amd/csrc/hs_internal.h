@@ -184,6 +184,28 @@ inline bool team_geom(int B, int N, int K, int64_t V, int dtype, TeamGeom* g) {
   return g->items < ((int64_t)1 << 31) && (int64_t)g->G * g->nsub < ((int64_t)1 << 26);
 }
 
+// The streaming argmax kernel's split of a call (hs_argmax.hip): rows of S units of 64 * kArgmaxStep
+// vectors, groups of per_group units, spans of `span` units, one per wave.
+constexpr int kArgmaxStep = 8;  // 16-byte loads of a unit per lane
+// Waves of a launch, when there are units enough: the device holds 4096 to 6144 of them at once, and
+// more and shorter spans only add arrivals (142 us with 4096 and 6144, 153 with 12288).
+constexpr int64_t kArgmaxWaves = 4096;
+struct ArgmaxPlan {
+  int S;
+  int64_t per_group, total, span;
+  int64_t pieces;  // of a row at most
+};
+inline ArgmaxPlan argmax_plan(const TeamGeom& g) {
+  ArgmaxPlan p;
+  const int64_t unit = 64 * kArgmaxStep;
+  p.S = (int)((g.nvec + unit - 1) / unit);
+  p.per_group = (int64_t)(g.N + 1) * p.S;
+  p.total = g.G * p.per_group;
+  p.span = (p.total + kArgmaxWaves - 1) / kArgmaxWaves;
+  p.pieces = (p.S + p.span - 2) / p.span + 1;
+  return p;
+}
+
 // Statistics of one row slice, in log2 units: offset o = fl(m * c) with c = log2(e)/T and
 // s = sum_v exp2(z_v * c - o); every exponent is formed by one fused multiply-add against the
 // same offset, so slices and threads combine exactly whatever the rounding of o.

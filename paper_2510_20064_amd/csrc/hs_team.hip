@@ -195,6 +195,28 @@ __device__ __forceinline__ void publish_norm(const TeamArgs& A, int set, int rr,
   }
 }
 
+// Publishes the argmax idx of row rr of row set `set` (tt: tag and taint) and writes the argmax and
+// agreement outputs (one lane).
+template <int D>
+__device__ __forceinline__ void put_argmax(const TeamArgs& A, int set, int rr, int b, int k, int sub,
+                                           int idx, uint32_t tag, uint32_t tt) {
+  uint64_t* norms = A.norm + (int64_t)set * (D + 1) * 3;
+  put_word(norms + 3 * rr + 2, word_of(idx, tt));
+  if (rr == 0) {
+    if (sub == 0 && A.argmax_t) A.argmax_t[(int64_t)b * A.K + k] = idx;
+    return;
+  }
+  const int64_t oi = ((int64_t)b * A.N + sub * D + rr - 1) * A.K + k;
+  if (A.argmax_d) A.argmax_d[oi] = idx;
+  if (A.agree) {
+    const uint64_t tw = await_word(norms + 2, tag, A);
+    const int it = word_i(tw);
+    const bool ag = idx == it && it >= 0;
+    A.agree[oi] = (uint8_t)ag;
+    if (A.learn == 2) put_word(A.gw + oi, word_of(ag ? 1.0f : 0.0f, tt | ((uint32_t)tw & kTaint)));
+  }
+}
+
 // Fold of row rr of row set `set`: the S slice statistics, two slices per lane per pass
 // (lane j takes slices j, j + 64, ... in order), then the wave. Publishes the row's log2
 // normaliser as hi + lo (in NC copies) and its argmax; writes the argmax and agreement
@@ -267,24 +289,42 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
   sum = wave_sum_f(sum);
   const uint32_t tt = tag | taint_bits(__ballot(lost) != 0);
   publish_norm<D, NC>(A, set, rr, ro, sum, tt, lane);
-  uint64_t* nw = A.norm + ((int64_t)set * RM + rr) * 3;
-  if (lane != 0) return;
-  if (NEED_ARG) {
-    put_word(nw + 2, word_of(idx, tt));
-    if (rr == 0) {
-      if (sub == 0 && A.argmax_t) A.argmax_t[(int64_t)b * A.K + k] = idx;
-    } else {
-      const int64_t oi = ((int64_t)b * A.N + sub * D + rr - 1) * A.K + k;
-      if (A.argmax_d) A.argmax_d[oi] = idx;
-      if (A.agree) {
-        const uint64_t tw = await_word(A.norm + (int64_t)set * RM * 3 + 2, tag, A);
-        const int it = word_i(tw);
-        const bool ag = idx == it && it >= 0;
-        A.agree[oi] = (uint8_t)ag;
-        if (A.learn == 2) put_word(A.gw + oi, word_of(ag ? 1.0f : 0.0f, tt | ((uint32_t)tw & kTaint)));
+  if (NEED_ARG && lane == 0) put_argmax<D>(A, set, rr, b, k, sub, idx, tag, tt);
+}
+
+// The argmax-only kernel's fold of row rr of row set `set`.
+template <int D>
+__device__ __forceinline__ void fold_row_argmax(const TeamArgs& A, int set, int rr, int b, int k,
+                                                int sub, uint32_t tag, int lane) {
+  const int S = A.S;
+  const uint64_t* base = stat_row(A, set, rr, D + 1);
+  float m = -INFINITY;
+  int idx = INT_MAX;
+  bool lost = false;
+  for (int j0 = 0; j0 < S; j0 += 128) {
+    uint64_t w[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {  // issue every load of the pass before waiting on any
+      const int j = j0 + lane + 64 * h;
+      if (j < S) {
+        w[h][0] = get_word(base + j);
+        w[h][1] = get_word(base + 2 * S + j);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int j = j0 + lane + 64 * h;
+      if (j < S) {
+        if (tag_of(w[h][0]) != tag) w[h][0] = await_word(base + j, tag, A);
+        if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + 2 * S + j, tag, A);
+        lost |= tainted(w[h][0]) || tainted(w[h][1]);
+        argmax_combine(m, idx, word_f(w[h][0]), word_i(w[h][1]));
       }
     }
   }
+  wave_max<true>(m, idx);
+  const uint32_t tt = tag | taint_bits(__ballot(lost) != 0);
+  if (lane == 0) put_argmax<D>(A, set, rr, b, k, sub, idx, tag, tt);
 }
 
 // Position of work item (set, slot): row set, slice, group (b, k), drafters n in the set, and
@@ -474,6 +514,26 @@ __device__ __forceinline__ float max_or_nan(const float (&z)[E]) {
   return m;
 }
 
+// Max of a thread's logits of one row and its lowest index, to LDS.
+template <int E, typename L>
+__device__ __forceinline__ float thread_argmax(const TeamArgs& A, const ItemPos& q, int r,
+                                               const float (&z)[E], L& sh, int t) {
+  float m = -INFINITY;
+  int idx = INT_MAX;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    if (z[e] > m) {
+      m = z[e];
+      idx = q.vi * E + e;
+    }
+  }
+  // a lane whose logits are all -inf still owns its lowest valid index
+  if (idx == INT_MAX && q.vi < A.nvec) idx = q.vi * E;
+  sh.xt[r][t] = m;
+  sh.xi[r][t] = idx;
+  return m;
+}
+
 // ---- 1. per-thread statistics of every row of item q in one pass, to LDS: the exp2 sum against the
 // thread's own offset (KEPT: the e_v stay in x) and, with NEED_ARG, the max and its lowest index.
 // An offset per thread needs no pass and no barrier before the sums, and keeps the exponents of
@@ -489,22 +549,9 @@ __device__ __forceinline__ void thread_stats(const TeamArgs& A, const ItemPos& q
     launder(raw[r]);
     float z[E];
     Vec<DT>::unpack(raw[r], z);
-    float m = -INFINITY;
-    if (NEED_ARG) {
-      int idx = INT_MAX;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if (z[e] > m) {
-          m = z[e];
-          idx = q.vi * E + e;
-        }
-      }
-      // a lane whose logits are all -inf still owns its lowest valid index
-      if (idx == INT_MAX && q.vi < A.nvec) idx = q.vi * E;
-      sh.xt[r][t] = m;
-      sh.xi[r][t] = idx;
-    }
-    if (!NEED_ARG) m = max_or_nan(z);
+    float m;
+    if (NEED_ARG) m = thread_argmax<E>(A, q, r, z, sh, t);
+    else m = max_or_nan(z);
     const float of = thread_offset(m, A.c);
     sh.xo[r][t] = (int)of;
     float v[E];
@@ -1176,6 +1223,93 @@ __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team
   finish(A, tag, leader, teams, sh, t);
 }
 
+// ---- argmax and agreement alone, few items per workgroup ----
+// Teams as above, one exchange per item: maxima and argmaxes are published and folded, while the next
+// item's loads fly. With few items per workgroup this is faster than the streaming argmax kernel
+// (hs_argmax.hip), where all waves of a group count their arrival at one word (some 80 ns each) and
+// one wave folds the group: launch_team_argmax says where the line lies.
+template <int D>
+struct ArgmaxLds {
+  float xt[D + 1][kThreads];  // per-thread maxima
+  int xi[D + 1][kThreads];    // per-thread argmax
+  uint32_t next;
+  const char* ptr[kMaxRows];
+  int64_t sb[kMaxRows];
+  int64_t sk[kMaxRows];
+};
+template <int DT, int D>
+__global__ __launch_bounds__(kThreads, 4) void hs_team_argmax_kernel(TeamArgs A) {
+  using Raw = typename Vec<DT>::Raw;
+  constexpr int RM = D + 1, E = Vec<DT>::kElems;
+  __shared__ ArgmaxLds<D> sh;
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int gi = t >> 4, gl = t & 15;
+  // every scalar the first loads depend on, requested in one round at entry
+  asm volatile("" ::"s"(A.N), "s"(A.K), "s"(A.nsub), "s"(A.S), "s"(A.items), "s"(A.teams),
+               "s"(A.uni), "s"(A.divS.m), "s"(A.divS.s1), "s"(A.divS.s2), "s"(A.divK.m),
+               "s"(A.divK.s1), "s"(A.divK.s2), "s"(A.V), "s"(A.epoch));
+  const int teams = A.teams;
+  const int T = (int)fdiv(blockIdx.x, A.divS), slot = (int)blockIdx.x - T * A.S;
+  const uint32_t nsets = fdiv((uint32_t)A.items, A.divS);
+  // slot 0 folds row 0 of every item, so it waits for the whole team each item: it can never
+  // be more than one item ahead of any member, which keeps a ring of 4 mailbox words safe
+  const bool leader = slot == 0;
+  const bool dynamic = 2 * teams < (int)nsets;  // else no team has more than its two fixed sets
+  uint64_t* mbox = A.mbox + (size_t)T * 4;
+  if (t < kMaxRows) {
+    sh.ptr[t] = reinterpret_cast<const char*>(A.rows.ptr[t]);
+    sh.sb[t] = A.rows.sb[t];
+    sh.sk[t] = A.rows.sk[t];
+  }
+  __syncthreads();
+  Raw nxt[RM];
+  uint32_t set = (uint32_t)T, next = min((uint32_t)(T + teams), nsets);
+  fetch_item<DT, D>(A, item_pos(A, set, slot, D), true, sh, nxt);
+  const uint32_t tag = call_tag(A.epoch);  // first needed once the first loads are in flight
+  for (int j = 0; set < nsets; ++j) {
+    const ItemPos q = item_pos(A, set, slot, D);
+    __builtin_amdgcn_s_setprio(kCritPrio);
+    mask_tail<DT, D>(A, q, nxt);
+#pragma unroll
+    for (int r = 0; r <= D; ++r) {
+      if (r > q.n) continue;
+      float z[E];
+      Vec<DT>::unpack(nxt[r], z);
+      thread_argmax<E>(A, q, r, z, sh, t);
+    }
+    // the team's item j + 1 (claimed two items ago), all waves alike after the barrier
+    if (j >= 1 && t == 0) sh.next = dynamic ? await_mbox(mbox + ((j + 1) & 3), j + 1, tag, A, nsets) : nsets;
+    // leader: claim the row set of item j + 2 and post it (the counter starts past every team's
+    // fixed sets, so a set is never claimed twice)
+    if (dynamic && leader && t == 0) {
+      const uint32_t v = (uint32_t)(2 * teams) +
+                         __hip_atomic_fetch_add(A.next_set, 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+      put_word(mbox + ((j + 2) & 3), mbox_word(min(v, nsets), j + 2, tag));
+    }
+    __syncthreads();
+    if (j >= 1) next = sh.next;
+    if (next < nsets) fetch_item<DT, D>(A, item_pos(A, next, slot, D), true, sh, nxt);
+    if (wv * 4 <= q.n) {
+      float m;
+      int idx;
+      group_argmax(sh, q.n, gi, gl, m, idx);
+      if (gl == 0 && gi <= q.n) {
+        uint64_t* wp = stat_row(A, q.set, gi, RM) + q.s;
+        put_word(wp, word_of(m, tag));
+        put_word(wp + 2 * A.S, word_of(idx, tag));
+      }
+    }
+    // the folds (fold_item's order), the duty wave first
+    for (int rr = q.s + ((wv + kWaves - kDutyWave) % kWaves) * A.S; rr <= q.n; rr += kWaves * A.S)
+      fold_row_argmax<D>(A, q.set, rr, q.b, q.k, q.sub, tag, lane);
+    __builtin_amdgcn_s_setprio(0);
+    __syncthreads();  // the LDS rows are free for the next item
+    set = next;
+  }
+  finish(A, tag, leader, teams, sh, t);
+}
+
 // ---- host side -------------------------------------------------------------------------------
 
 namespace {
@@ -1188,21 +1322,24 @@ std::atomic<uint32_t> g_wait_polls{kDefaultPolls};
 uint32_t wait_polls() { return g_wait_polls.load(std::memory_order_relaxed); }
 
 // Workgroups of the team kernel the current device holds at once.
-template <int DT, int D, bool NA, bool SG, bool CO>
-int capacity_t() {
-  static std::atomic<int> cached[64];  // per device; 0 = not yet known
+template <typename K>
+int capacity_of(K kernel, std::atomic<int> (&cached)[64]) {  // cached per device; 0 = not yet known
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
   int v = cached[dev].load(std::memory_order_relaxed);
   if (v > 0) return v;
   int per_cu = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, hs_team_kernel<DT, D, NA, SG, CO>,
-                                                   kThreads, 0) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
   v = per_cu * cus;
   cached[dev].store(v, std::memory_order_relaxed);
   return v;
+}
+template <int DT, int D, bool NA, bool SG, bool CO>
+int capacity_t() {
+  static std::atomic<int> cached[64];
+  return capacity_of(hs_team_kernel<DT, D, NA, SG, CO>, cached);
 }
 
 // Runs the team kernel with as many teams as the device holds at once (no more than there are
@@ -1234,6 +1371,29 @@ int launch_t(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* learned) {
   else if (common) hs_team_kernel<DT, D, NA, false, !NA><<<(unsigned)P, kThreads, 0, stream>>>(A);
   else hs_team_kernel<DT, D, NA, false, false><<<(unsigned)P, kThreads, 0, stream>>>(A);
   return HS_OK;
+}
+
+// Argmax and agreement by the team kernel where it is the faster (*taken), else nothing. The streaming
+// kernel is, also for the smallest calls, where a group has few units (at most 20: 64 queries x 8
+// drafters x 8 positions x 4000 bf16 logits 15.7 us, by teams 27.6) or teams would claim items beyond
+// their two fixed ones (us, streaming and teams, at items per resident workgroup: 16 x 5 x 7 x 50257
+// 17.9 and 47.4 at 2.2, 64 x 4 x 4 x 32000 21.4 and 42.6 at 2.7, 24 x 8 x 6 x 128256 63 and 76 at
+// 7.1). Below that its waves, which all count their arrival at their group's word, cost more than they
+// stream: 1 x 8 x 8 x 151936 46 and 10.3, 12 x 5 x 7 x 50257 32 and 19.5 at 1.6; with more than 62 of
+// them to a group up to about six items (6 x 8 x 6 x 128256 fp32 68 and 39 at 3.5, 8 53 and 49.5 at
+// 4.7, 12 58 and 78 at 7.1).
+template <int DT, int D>
+int launch_team_argmax(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* taken) {
+  static std::atomic<int> cached[64];
+  const int cap = capacity_of(hs_team_argmax_kernel<DT, D>, cached);
+  const ArgmaxPlan p = argmax_plan(g);
+  const int64_t sets = g.items / g.S, teams = std::min<int64_t>({cap / g.S, sets, (int64_t)kMaxTeams});
+  *taken = teams > 0 && p.per_group > 20 && sets <= (p.per_group <= 62 * p.span ? 2 : 6) * teams;
+  if (!*taken) return HS_OK;
+  A.learn = 0;
+  A.teams = (int)teams;
+  hs_team_argmax_kernel<DT, D><<<(unsigned)(A.teams * g.S), kThreads, 0, stream>>>(A);
+  return hipGetLastError() == hipSuccess ? HS_OK : HS_ERR_HIP;
 }
 
 // Calls F<DT, D, NA>::run(args...) for the geometry and mode.
@@ -1271,6 +1431,13 @@ struct Launch {
   }
 };
 
+template <int DT, int D, bool NA>
+struct LaunchArgmax {
+  static int run(const TeamArgs& A, const TeamGeom& g, hipStream_t s, bool* taken) {
+    return launch_team_argmax<DT, D>(A, g, s, taken);
+  }
+};
+
 }  // namespace
 
 void set_wait_polls(int polls) {
@@ -1295,10 +1462,6 @@ int launch_round(const TeamGeom& g, const RowTable& rows, float c, bool need_sum
     a.round_fail = A.fail;
     return launch_tail(a, stream);
   };
-  if (!need_sum) {
-    const int rc = launch_argmax(g, rows, agree, argmax_t, argmax_d, wait_polls(), ws, stream);
-    return rc || !tail ? rc : tail_after();
-  }
   A.rows = rows;
   A.base0 = rows.ptr[0];
   A.base1 = rows.ptr[1];
@@ -1348,6 +1511,12 @@ int launch_round(const TeamGeom& g, const RowTable& rows, float c, bool need_sum
   // the gamma words (the learner step in the same launch); the single-item kernel's extra
   // normaliser copies follow them
   A.gw = reinterpret_cast<uint64_t*>(ws + L.gw);
+  if (!need_sum) {
+    bool taken = false;
+    int rc = dispatch<LaunchArgmax>(g, true, A, g, stream, &taken);
+    if (!rc && !taken) rc = launch_argmax(g, rows, agree, argmax_t, argmax_d, A.polls, ws, stream);
+    return rc || !tail ? rc : tail_after();
+  }
   if (tail) {  // the learner step in the same launch, when its LDS fits
     A.learn = tail->gamma_src;
     A.tail = *tail;
