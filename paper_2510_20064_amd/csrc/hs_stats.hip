@@ -111,13 +111,24 @@ void launch_rows(const char* x, int64_t rows, int64_t V, int64_t ld, int64_t nve
                  float* row_max, float* row_lse, int32_t* row_argmax, hipStream_t stream) {
   constexpr int U = Vec<DT>::kU;
   // A workgroup keeps 2 U 16-byte loads per thread in flight, and few rows of 256 threads are fewer
-  // than the memory needs. 128256 bf16 logits, 256 and 1024 threads: 8 rows of 151936 38.7 and 20.5
-  // us, 64 rows 42.6 and 19.9, 384 48.8 and 32.5, 700 56.7 and 46.2, 1024 64.0 and 60.5, 1536 80.3
-  // and 86.3. Rows of 30000 (a chunk of 1024 threads is half of one): 384 rows 15.5 and 13.8, 900
-  // 21.0 and 23.4; of 64000, 900 rows 36.8 and 35.8. 32000 fp32 logits: 384 rows 17.6 and 16.2, 1536
-  // 43.0 and 39.2, 3000 74.4 and 69.5; 3500 rows of 30000 80.5 and 80.1.
-  const int64_t few = DT == HS_F32 ? 3072 : nvec >= 8000 ? 1024 : 512;
-  if (rows < few)
+  // than the memory needs; but 1024 threads on a row shorter than their chunk mostly start and end,
+  // and 512 workgroups of them fill the device, so that a few rows more take a second round.
+  // us with 256 and 1024 threads:
+  // up to 256 rows, from 4/5 of a chunk of 1024 threads on: 64 rows of 151936 bf16 logits 50.6 and
+  //   22.2, of 16000 7.9 and 6.7, of 14000 7.7 and 6.7, of 12000 6.5 and 6.6, of 8000 5.2 and 6.4, of
+  //   1000 4.2 and 6.0; 256 of 14000 fp32 9.2 and 8.3, of 12000 7.7 and 8.0;
+  // up to 511, from 1 1/2 chunks on: 384 rows of 128256 bf16 48.8 and 32.5, 400 of 25000 13.4 and 13.1,
+  //   of 20000 10.7 and 12.1, of 1000 4.2 and 7.9; of 25000 fp32 15.1 and 14.9, of 20000 12.1 and 13.8;
+  // up to 1023, 16-bit rows of 64000 on: 700 of 152000 63.2 and 49.8, of 64000 30.1 and 26.9, 1023
+  //   34.2 and 33.9; 1500 of 64000 43.5 and 44.2;
+  // 1200 to 3071, fp32 rows of 50000 on: 1500 of 64000 72.6 and 69.3, 2500 119 and 108, of 50000 95 and
+  //   89; 700 of 64000 36.0 and 37.2; 2000 of 40000 54.6 and 58.6, of 1000 7.4 and 24.4.
+  constexpr int64_t kChunk = 1024 * U;
+  const bool wide = rows <= 256         ? 5 * nvec >= 4 * kChunk
+                    : rows < 512        ? 2 * nvec >= 3 * kChunk
+                    : DT == HS_F32      ? nvec >= 12500 && rows >= 1200 && rows < 3072
+                                        : nvec >= 8000 && rows < 1024;
+  if (wide)
     hs_softmax_stats_kernel<DT, 1024, U><<<(unsigned)rows, 1024, 0, stream>>>(
         x, ld, V, nvec, c, row_max, row_lse, row_argmax);
   else

@@ -107,3 +107,29 @@ def test_row_statistics_by_row_count(rows, V, dtype):
     assert np.array_equal(am.cpu().numpy(), np.argmax(x[:, :V].float().numpy(), axis=1))
     ref = torch.logsumexp(z / 0.7, dim=1)
     assert ((lse.cpu().double() - ref).abs() <= 1e-6 * (1 + ref.abs())).all()
+
+
+# both sides of every line of the rule: short and long rows of few, 16-bit rows of 64000 logits around
+# 1024 of them, fp32 rows of 50000 around 1200 and 3072. Bound as above, with 1.5e-6 for the longest
+# rows: sixteen times the terms per thread, whose sums round in turn
+@pytest.mark.parametrize("dtype,rows,V", [
+    ("bf16", 256, 13103), ("bf16", 256, 13112), ("f32", 256, 13100), ("f32", 256, 13108),
+    ("bf16", 257, 24569), ("bf16", 511, 24576), ("f32", 300, 24570), ("f32", 511, 24577),
+    ("f16", 1023, 64000), ("bf16", 1024, 64001), ("bf16", 700, 63990), ("f16", 512, 64007),
+    ("f32", 1199, 50001), ("f32", 1200, 50000), ("f32", 1200, 49995), ("f32", 512, 50003),
+    ("f32", 3071, 50000), ("f32", 3072, 50000)])
+def test_row_statistics_at_the_lines_of_the_rule(rows, V, dtype):
+    note("stats %s rows=%d V=%d" % (dtype, rows, V))
+    g = torch.Generator(device="cuda:0").manual_seed(rows + V)
+    x = (torch.randn((rows, (V + 7) // 8 * 8), generator=g, device="cuda:0") * 3.0).to(DTYPES[dtype])
+    x[rows // 2, V - 1] = 40.0
+    mx, lse, am = hs.softmax_stats(x, V=V, temperature=0.7)
+    torch.cuda.synchronize()
+    for r in range(0, rows, 256):
+        z = x[r:r + 256, :V].float()
+        top = z.amax(1)
+        first = torch.where(z == top[:, None], torch.arange(V, device=z.device), V).amin(1)
+        assert torch.equal(mx[r:r + 256], top)
+        assert torch.equal(am[r:r + 256].long(), first)
+        ref = torch.logsumexp(z.double() / 0.7, dim=1)
+        assert ((lse[r:r + 256].double() - ref).abs() <= 1.5e-6 * (1 + ref.abs())).all()
