@@ -4,7 +4,8 @@
 //      takes a span of it, one unit in registers and the next one's loads in flight, and
 //      publishes the maximum of each row's piece and the vector that holds it, as tagged words;
 //   2. the wave that arrives last at a group folds the group's rows, reads the one vector that
-//      holds each row's maximum for the element, and writes the argmaxes and agreements.
+//      holds each row's maximum for the element, and writes the argmaxes and agreements; the one
+//      that folds the last group marks every output when a wait of any fold has given up.
 // Bound by HBM: 64 queries x 8 drafters x 6 positions x 128256 bf16 logits in 142 us (6.2 TB/s; the
 // card streams 7.0). The argmax variant of the team kernel, whose members wait for each other's
 // words between the loads of one item and the next, takes 189 us; it takes the calls with few items
@@ -46,12 +47,35 @@ __device__ __forceinline__ const char* row_ptr(const ArgmaxArgs& A, int r, int g
          ((int64_t)b * A.rows.sb[r] + (int64_t)k * A.rows.sk[r]) * Vec<DT>::kBytes;
 }
 
-// Folds group g (one wave, lane r: row r): its pieces' words, then the element of each maximum.
+// In the count of folded groups: a wait of one of these folds has given up.
+constexpr uint32_t kFailed = 1u << 31;
+
+// Output stores go past the caches of this XCD, so that marks written by another one after them
+// (mark_all) are what memory holds in the end.
+template <typename T>
+__device__ __forceinline__ void put_out(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every output of the call invalid (one wave).
+__device__ inline void mark_all(const ArgmaxArgs& A, int lane) {
+  const int64_t outs = (int64_t)A.G * A.N;
+  for (int64_t o = lane; o < outs; o += 64) {
+    if (A.agree) put_out(A.agree + o, (uint8_t)0);
+    if (A.argmax_d) put_out(A.argmax_d + o, -2);
+  }
+  if (A.argmax_t)
+    for (int64_t o = lane; o < A.G; o += 64) put_out(A.argmax_t + o, -2);
+}
+
+// Folds group g (one wave, lane r: row r): its pieces' words, then the element of each maximum. True for
+// the call's last fold when this or another one has lost a word.
 template <int DT>
-__device__ __forceinline__ void fold_group(const ArgmaxArgs& A, int g, uint32_t tag, int lane) {
+__device__ __forceinline__ bool fold_group(const ArgmaxArgs& A, int g, uint32_t tag, int lane) {
   const int R = A.N + 1;
   const int b = (int)fdiv((uint32_t)g, A.divK), k = g - b * A.K;
   int target = -2;
+  bool gone = false;  // a word of this group is lost
   for (int r0 = 0; r0 < R; r0 += 64) {
     const int r = r0 + lane;
     int e = -2;
@@ -80,25 +104,37 @@ __device__ __forceinline__ void fold_group(const ArgmaxArgs& A, int g, uint32_t 
         }
       }
       if (!lost) e = argmax_element<DT>(row_ptr<DT>(A, r, g), A.V, A.nvec, m, idx);
+      gone |= lost;
     }
     if (r0 == 0) target = __builtin_amdgcn_readfirstlane(e);
     if (r < R) {
       if (r == 0) {
-        if (A.argmax_t) A.argmax_t[(int64_t)b * A.K + k] = e;
+        if (A.argmax_t) put_out(A.argmax_t + (int64_t)b * A.K + k, e);
       } else {
         const int64_t o = ((int64_t)b * A.N + r - 1) * A.K + k;
-        if (A.argmax_d) A.argmax_d[o] = e;
-        if (A.agree) A.agree[o] = (uint8_t)(e == target && e >= 0);
+        if (A.argmax_d) put_out(A.argmax_d + o, e);
+        if (A.agree) put_out(A.agree + o, (uint8_t)(e == target && e >= 0));
       }
     }
   }
-  if (lane != 0) return;
-  // the last group to be folded advances the epoch and leaves its count open for the next call
-  if (tagged_add(A.finished, tag, kOpenPolls) == (uint32_t)A.G - 1u) {
-    const uint32_t e = *A.epoch + 1u;
-    put_word(A.finished, (uint64_t)tag_of_epoch(e));
-    *A.epoch = e;
+  const bool failed = __ballot(gone) != 0;
+  uint32_t n = 0;
+  if (lane == 0) {
+    if (failed) {  // before this group is counted, so that the last one sees it
+      open_count(A.finished, tag);
+      __hip_atomic_fetch_or(A.finished, (uint64_t)kFailed << 32, __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT);
+    }
+    n = tagged_add(A.finished, tag, kOpenPolls);
+    if ((n & ~kFailed) == (uint32_t)A.G - 1u) {
+      // the last group to be folded advances the epoch and leaves its count open for the next call
+      const uint32_t e = *A.epoch + 1u;
+      put_word(A.finished, (uint64_t)tag_of_epoch(e));
+      *A.epoch = e;
+    }
   }
+  // (a mark may still be followed by the store of a fold that lost nothing: its value is right)
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)n) == (kFailed | ((uint32_t)A.G - 1u));
 }
 
 template <int DT>
@@ -148,6 +184,7 @@ __global__ __launch_bounds__(kThreads, 4) void hs_argmax_kernel(ArgmaxArgs A) {
       lp = row_ptr<DT>(A, lr, min(lg, A.G - 1));
     }
   };
+  bool mark = false;  // (the call's last fold is its wave's last)
   float best = -INFINITY;
   int bi = c * 64 * kStep + lane < (int)A.nvec ? c * 64 * kStep + lane : INT_MAX;
   // uses unit u from x while the loads of the next go out to y; false after the span's last
@@ -195,7 +232,7 @@ __global__ __launch_bounds__(kThreads, 4) void hs_argmax_kernel(ArgmaxArgs A) {
         uint32_t n = 0;
         if (lane == 0) n = tagged_add(A.arrived + g, tag, kOpenPolls);
         if ((uint32_t)__builtin_amdgcn_readfirstlane((int)n) == waves - 1u)
-          fold_group<DT>(A, g, tag, lane);
+          mark = fold_group<DT>(A, g, tag, lane);
       }
       best = -INFINITY;
     }
@@ -227,6 +264,7 @@ __global__ __launch_bounds__(kThreads, 4) void hs_argmax_kernel(ArgmaxArgs A) {
     if (!step(x, y)) break;
     if (!step(y, x)) break;
   }
+  if (mark) mark_all(A, lane);
 }
 
 }  // namespace

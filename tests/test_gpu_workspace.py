@@ -72,3 +72,22 @@ def test_noalloc_for_changing_shapes_and_modes():
             torch.cuda.synchronize()
             for k in ref:
                 assert torch.equal(got[k], ref[k]), k
+
+
+@pytest.mark.parametrize("B,N,K,V", [(64, 8, 6, 4000), (48, 3, 8, 20011), (3, 19, 2, 700)])
+def test_streamed_greedy_call_with_a_wait_that_gave_up(B, N, K, V):
+    """A fold that loses a word marks its call's count of folded groups (byte 24, top bit) and every
+    output is invalid, those of the groups that lost nothing too. The mark is set here by the host."""
+    x = logits(B, N, K, V, V)
+    ws = hs.alloc_workspace(B, N, K, V, hs.HS_BF16, "cuda:0")
+    ref = outputs(x, V, hs.GREEDY, hs.eval_alpha, workspace=ws)
+    assert bool(ref["agree"][:, N - 1].all())
+    print("\n[case] failed fold B=%d N=%d K=%d V=%d" % (B, N, K, V), flush=True)
+    ws[31] |= 0x80
+    got = outputs(x, V, hs.GREEDY, hs.eval_alpha, workspace=ws)
+    assert int(got["agree"].sum()) == 0
+    assert bool((got["argmax_t"] == -2).all()) and bool((got["argmax_d"] == -2).all())
+    check_no_word_of_the_next_call(ws)
+    got = outputs(x, V, hs.GREEDY, hs.eval_alpha, workspace=ws)
+    for k in ref:
+        assert torch.equal(got[k], ref[k]), k
