@@ -116,9 +116,10 @@ int validate_eval(const EvalReq& q, hs::TeamGeom* g, hs::RowTable* rows) {
 }
 
 // The one check that asks the device, made after every host-side check: a team of S
-// workgroups must fit on the device at once (without alpha another kernel takes what does not).
+// workgroups must fit on the device at once (without alpha another kernel takes what does not,
+// unless the call is beyond its numbering).
 int check_capacity(const EvalReq& q, const hs::TeamGeom& g) {
-  if (!q.alpha) return HS_OK;
+  if (!q.alpha && hs::argmax_fits(hs::argmax_plan(g))) return HS_OK;
   const int cap = hs::team_capacity(g, q.agree || q.argmax_t || q.argmax_d);
   if (cap < g.S)
     return fail(HS_ERR_LIMIT, "the device holds %d evaluation workgroups at once, %d are needed",

@@ -205,6 +205,12 @@ inline ArgmaxPlan argmax_plan(const TeamGeom& g) {
   p.pieces = (p.S + p.span - 2) / p.span + 1;
   return p;
 }
+// The streaming kernel numbers units, up to a workgroup's spans past the last one, with int. A call with
+// more (many long rows at broadcast strides: 64 drafters have up to four times as many units as
+// the team kernel has items) goes by teams.
+inline bool argmax_fits(const ArgmaxPlan& p) {
+  return p.total + (int64_t)kWaves * p.span < ((int64_t)1 << 31);
+}
 
 // Statistics of one row slice, in log2 units: offset o = fl(m * c) with c = log2(e)/T and
 // s = sum_v exp2(z_v * c - o); every exponent is formed by one fused multiply-add against the

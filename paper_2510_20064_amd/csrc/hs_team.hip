@@ -1373,7 +1373,8 @@ int launch_t(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* learned) {
   return HS_OK;
 }
 
-// Argmax and agreement by the team kernel where it is the faster (*taken), else nothing. The streaming
+// Argmax and agreement by the team kernel where it is the faster, or the streaming kernel cannot number
+// the call's units (*taken), else nothing. The streaming
 // kernel is, also for the smallest calls, where a group has few units (at most 20: 64 queries x 8
 // drafters x 8 positions x 4000 bf16 logits 15.7 us, by teams 27.6) or teams would claim items beyond
 // their two fixed ones (us, streaming and teams, at items per resident workgroup: 16 x 5 x 7 x 50257
@@ -1388,8 +1389,10 @@ int launch_team_argmax(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* 
   const int cap = capacity_of(hs_team_argmax_kernel<DT, D>, cached);
   const ArgmaxPlan p = argmax_plan(g);
   const int64_t sets = g.items / g.S, teams = std::min<int64_t>({cap / g.S, sets, (int64_t)kMaxTeams});
-  *taken = teams > 0 && p.per_group > 20 && sets <= (p.per_group <= 62 * p.span ? 2 : 6) * teams;
+  const bool faster = p.per_group > 20 && sets <= (p.per_group <= 62 * p.span ? 2 : 6) * teams;
+  *taken = !argmax_fits(p) || (teams > 0 && faster);
   if (!*taken) return HS_OK;
+  if (teams <= 0) return HS_ERR_LIMIT;
   A.learn = 0;
   A.teams = (int)teams;
   hs_team_argmax_kernel<DT, D><<<(unsigned)(A.teams * g.S), kThreads, 0, stream>>>(A);

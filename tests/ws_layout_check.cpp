@@ -49,6 +49,30 @@ int main() {
     }
     CHECK(hs::tag_of_epoch(0xFFFFFFFFu) != hs::tag_of_epoch(0u));
   }
+  // The streaming argmax kernel numbers units with int, also those of its last workgroup's waves past
+  // the end: calls beyond that must not reach it, and of the others no number may overflow.
+  const long long calls[][5] = {{1, 8, 8, 151936, HS_BF16}, {32, 64, 8, 151936, HS_BF16},
+                                {1, 1, 1, 1, HS_F32},       {64, 8, 6, 128256, HS_BF16},
+                                {65535, 64, 64, 28672, HS_BF16}, {65535, 64, 64, 28673, HS_BF16},
+                                {65535, 64, 64, 32768, HS_BF16}, {65535, 33, 64, 100000, HS_F16},
+                                {65535, 64, 8, 500000, HS_F32},  {65535, 64, 63, 14337, HS_F32}};
+  bool beyond = false;
+  for (const auto& s : calls) {
+    hs::TeamGeom g;
+    if (!hs::team_geom((int)s[0], (int)s[1], (int)s[2], s[3], (int)s[4], &g)) continue;
+    const hs::ArgmaxPlan p = hs::argmax_plan(g);
+    const hs::TeamWs L = hs::team_ws(g);
+    // a row's words (two per piece) lie in the slice statistics' region
+    CHECK(L.stat + 16ull * g.G * (g.N + 1) * p.pieces <= L.norm);
+    const long long waves = (p.total + p.span - 1) / p.span;
+    const long long grid = (waves + hs::kWaves - 1) / hs::kWaves;
+    const bool overflows = p.total > INT32_MAX || grid * hs::kWaves * p.span > INT32_MAX ||
+                           p.per_group > INT32_MAX;
+    beyond |= overflows;
+    CHECK(!(overflows && hs::argmax_fits(p)));
+    if (s[0] < 100) CHECK(hs::argmax_fits(p));
+  }
+  CHECK(beyond);
   std::printf(fails ? "layout check: %d failures\n" : "layout check: ok\n", fails);
   return fails ? 1 : 0;
 }
