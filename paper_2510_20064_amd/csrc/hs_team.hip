@@ -78,7 +78,7 @@ struct TeamArgs {
   uint32_t* next_set;  // row sets claimed beyond each team's fixed ones
   uint64_t* finished;  // teams of this launch that have finished (a tagged count)
   uint64_t* mbox;      // [teams][4]: the row set of each team's coming items
-  uint64_t* stat;  // [sets][D + 1][S][3]
+  uint64_t* stat;  // [sets][D + 1][3][S]
   uint64_t* norm;  // [sets][D + 1][3] (the single-item kernel's other copies: norm_copy)
   uint64_t* part;  // [G][N][S]
   float* alpha;
@@ -292,7 +292,7 @@ __device__ __forceinline__ void fold_row(const TeamArgs& A, int set, int rr, int
   if (NEED_ARG && lane == 0) put_argmax<D>(A, set, rr, b, k, sub, idx, tag, tt);
 }
 
-// The argmax-only kernel's fold of row rr of row set `set`.
+// The argmax-only kernel's fold of row rr of row set `set`: a slice's two words side by side.
 template <int D>
 __device__ __forceinline__ void fold_row_argmax(const TeamArgs& A, int set, int rr, int b, int k,
                                                 int sub, uint32_t tag, int lane) {
@@ -307,16 +307,16 @@ __device__ __forceinline__ void fold_row_argmax(const TeamArgs& A, int set, int 
     for (int h = 0; h < 2; ++h) {  // issue every load of the pass before waiting on any
       const int j = j0 + lane + 64 * h;
       if (j < S) {
-        w[h][0] = get_word(base + j);
-        w[h][1] = get_word(base + 2 * S + j);
+        w[h][0] = get_word(base + 2 * j);
+        w[h][1] = get_word(base + 2 * j + 1);
       }
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int j = j0 + lane + 64 * h;
       if (j < S) {
-        if (tag_of(w[h][0]) != tag) w[h][0] = await_word(base + j, tag, A);
-        if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + 2 * S + j, tag, A);
+        if (tag_of(w[h][0]) != tag) w[h][0] = await_word(base + 2 * j, tag, A);
+        if (tag_of(w[h][1]) != tag) w[h][1] = await_word(base + 2 * j + 1, tag, A);
         lost |= tainted(w[h][0]) || tainted(w[h][1]);
         argmax_combine(m, idx, word_f(w[h][0]), word_i(w[h][1]));
       }
@@ -1273,6 +1273,7 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_argmax_kernel(TeamArgs A)
 #pragma unroll
     for (int r = 0; r <= D; ++r) {
       if (r > q.n) continue;
+      launder(nxt[r]);
       float z[E];
       Vec<DT>::unpack(nxt[r], z);
       thread_argmax<E>(A, q, r, z, sh, t);
@@ -1295,9 +1296,9 @@ __global__ __launch_bounds__(kThreads, 4) void hs_team_argmax_kernel(TeamArgs A)
       int idx;
       group_argmax(sh, q.n, gi, gl, m, idx);
       if (gl == 0 && gi <= q.n) {
-        uint64_t* wp = stat_row(A, q.set, gi, RM) + q.s;
+        uint64_t* wp = stat_row(A, q.set, gi, RM) + 2 * q.s;
         put_word(wp, word_of(m, tag));
-        put_word(wp + 2 * A.S, word_of(idx, tag));
+        put_word(wp + 1, word_of(idx, tag));
       }
     }
     // the folds (fold_item's order), the duty wave first
