@@ -39,7 +39,8 @@ HBM_PEAK_GBS = 8000.0
 ROTATE_BYTES = 512 * 1024 * 1024
 METRIC = "drafter-positions evaluated/sec + achieved HBM GB/s (% of peak), 1 MI355X"
 # Sources of the evaluation kernels; a counter summary is valid only for these bytes.
-KERNEL_SOURCES = ["paper_2510_20064_amd/csrc/hs_team.hip", "paper_2510_20064_amd/csrc/hs_wave.h",
+KERNEL_SOURCES = ["paper_2510_20064_amd/csrc/hs_team.hip", "paper_2510_20064_amd/csrc/hs_argmax.hip",
+                  "paper_2510_20064_amd/csrc/hs_exchange.h", "paper_2510_20064_amd/csrc/hs_wave.h",
                   "paper_2510_20064_amd/csrc/hs_internal.h", "paper_2510_20064_amd/csrc/hs_learner.h"]
 
 
@@ -712,7 +713,7 @@ def main():
                    "wall_s": round(wall, 4)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(profile_name(w, name)),
-                     "kernel": "hs_eval_alpha = hs_team_kernel (one launch)",
+                     "kernel": "hs_eval_alpha (one launch)",
                      "kernel_us": eval_us, "kernel_calls_timed": n_eval,
                      "algorithmic_bytes_per_launch": w.input_bytes,
                      "step_us": ms_step * 1e3},

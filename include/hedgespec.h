@@ -56,8 +56,9 @@ extern "C" {
 #define HS_MAX_TOPL 32      /* L: children per draft-tree node in hs_eval_topl           */
 #define HS_MAX_CANDIDATES 1024 /* C: candidate slots per node in hs_candidate_mass       */
 /* V: at most 512 * 256 16-byte vectors per row (1048576 bf16 or fp16, or 524288 fp32
-   logits), and the device must hold ceil(V / 2048) (bf16, fp16) or ceil(V / 1024) (fp32)
-   evaluation workgroups at once: hs_eval_alpha returns HS_ERR_LIMIT otherwise. */
+   logits), and for alpha the device must hold ceil(V / 2048) (bf16, fp16) or ceil(V / 1024)
+   (fp32) evaluation workgroups at once: hs_eval_alpha returns HS_ERR_LIMIT otherwise. Agreement
+   and argmaxes alone need that only for calls of 2^31 and more 8 KB pieces of rows. */
 
 /* ---- enumerations ------------------------------------------------------------------------- */
 #define HS_F32 0  /* fp32 logits                            */

@@ -109,9 +109,9 @@ __device__ __forceinline__ float max_elems(const float (&z)[E]) {
 }
 
 // Lowest index of a logit equal to m in 16-byte vector vi of the row at p (m the vector's maximum; -inf:
-// the vector's first logit). The slices exchange the vector that holds their maximum and the
-// fold reads that one vector, so that no thread tracks an element index along its logits (three
-// instructions per logit: 216 of a thread's 700 per item with alpha).
+// the vector's first logit). The waves of the streaming argmax kernel exchange the vector that holds
+// their maximum and the fold reads that one vector, so that no thread tracks an element index along
+// its logits (three instructions per logit, where taking the maximum costs half of one).
 template <int DT>
 __device__ __forceinline__ int argmax_element(const char* p, int64_t V, int64_t nvec, float m,
                                               int vi) {

@@ -230,8 +230,11 @@ struct TeamWs {
   size_t epoch;  // control block: uint32 call counter at +0, the call's fail flag (word) at
                  // +8, the row-set count (tagged word) at +16, the count of teams that have
                  // finished (tagged word) at +24, then a ring of 4 mailbox words per team at +64
-  size_t stat;   // [G * nsub][D + 1][S][3] words: slice max, exp2 sum, argmax
-  size_t norm;   // [G * nsub][D + 1][3] words: log2 normaliser hi, lo, argmax
+  size_t stat;   // [G * nsub][D + 1][3][S] words: slice offset (max, where there are argmaxes),
+                 // exp2 sum, argmax; without alpha [S][2] (max, argmax) of these, or the
+                 // streaming argmax kernel's words per row piece
+  size_t norm;   // [G * nsub][D + 1][3] words: log2 normaliser hi, lo, argmax; the argmax kernel's
+                 // counts (arrived)
   size_t norm_copy;  // bytes of one copy of them (kNormCopies - 1 more follow the gamma words)
   size_t part;   // [G][N][S] words: per-slice sums of min(p, q_i)
   size_t gw;     // [B][N][K] words: gamma (alpha or agreement) for a learner in the same launch

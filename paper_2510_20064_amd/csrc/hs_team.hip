@@ -1005,9 +1005,9 @@ __device__ __forceinline__ void finish(const TeamArgs& A, uint32_t tag, bool cou
 // COMMON (pipelined, without an argmax): sums against one common offset where they fit it.
 // SINGLE: every team has exactly one item, so nothing is pipelined, the
 // e_v stay in registers and drafters at a constant distance are addressed without the table.
-// With an argmax as well the pipelined kernel runs 3 workgroups per CU: held to the 128 registers of
-// a fourth it spills 140 bytes and runs 58 us instead of 45 (13 queries x 5 drafters x 7 positions x
-// 50257 fp16 logits).
+// With an argmax as well the pipelined kernel's LDS (47 KB with 8 drafters) leaves room for 3 workgroups
+// per CU, and it takes the registers (140) that this leaves; its bound says so (43.9 us and, with a
+// bound of 4, 44.3 for 13 queries x 5 drafters x 7 positions x 50257 fp16 logits).
 template <int DT, int D, bool NEED_ARG, bool SINGLE, bool COMMON>
 __global__ __launch_bounds__(kThreads, NEED_ARG && !SINGLE ? 3 : 4) void hs_team_kernel(TeamArgs A) {
   using Raw = typename Vec<DT>::Raw;

@@ -1,10 +1,13 @@
-"""The argmax kernel (greedy mode without alpha) and the alpha kernel's two ways of taking a row's
-sum, at the sizes where their dispatch turns.
+"""Greedy calls without alpha (the streaming argmax kernel and the team kernel's argmax variant), the
+alpha kernel's sums against a common offset and against a thread's own, and the row statistics, at
+the sizes where their dispatch turns.
 
 The argmax kernel cuts rows into units of 512 16-byte vectors and gives waves spans of units, so
 the edges are rows of one vector, of a partial vector only, of one unit and one logit more, and
-batches whose spans cross rows and groups. The alpha kernel takes sums against offset 0 and
-retries a row whose sum leaves [2^-64, 2^64]: logits shifted by multiples of 40 cross both ends.
+batches whose spans cross rows and groups. The alpha kernel with several items per workgroup takes
+a thread's sums of up to 8 terms against a common offset of 8 binary orders at T = 1 (5.5 logits)
+and an item again, by its threads' largest logits, where a sum leaves [2^-56, 2^96]: logits near
+-33 and +72, which shifts by multiples of 40 cross for some rows of an item and not for others.
 """
 import numpy as np
 import pytest
@@ -72,10 +75,12 @@ def test_argmax_and_agreement(B, N, K, V, kind, dtype):
 @pytest.mark.parametrize("shift", [-120.0, -80.0, -40.0, 40.0, 80.0])
 @pytest.mark.parametrize("B,N,K,V", [(1, 8, 2, 4104), (1, 3, 2, 4104), (48, 8, 4, 32000)])
 def test_sums_outside_the_plain_range(B, N, K, V, shift, dtype):
-    # some rows shifted (a softmax does not see it), so that plain and retried rows share items;
-    # 48 queries run the pipelined kernel, one the kernel with one item per workgroup. A logit near
-    # 128 has an exponent rounded at 2^-18 (1.3e-5 of its term after the factor ln 2, twice for
-    # target and drafter, and a sum averages them): 2e-5 absolute, as for every alpha here
+    # some rows shifted (a softmax does not see it), so that rows against the common offset and
+    # against their threads' own share items; 48 queries run the pipelined kernel, one the kernel
+    # with one item per workgroup, whose exponents lie near 0: 2^-25 each, with exp2, two sums and
+    # two logarithms 2^-24 each, within 1.5e-6. The pipelined kernel's exponents reach 96 against the
+    # common offset (rounded at 2^-18: 2.6e-6 of a term after the factor ln 2, at random from term
+    # to term), and the min-sums' 64, for target and drafter (2^-19, 1.3e-6 each): within 5e-6
     note("shift %g %s B=%d N=%d" % (shift, dtype, B, N))
     x = logits((N + 1, B, K, V), "f32", 11, "plain")
     x = (x * 8).round() / 8
@@ -90,7 +95,7 @@ def test_sums_outside_the_plain_range(B, N, K, V, shift, dtype):
     out = hs.eval_alpha(x.to("cuda:0"), V=V, temperature=1.0, mode=hs.SAMPLE, want_alpha=True)
     torch.cuda.synchronize()
     err = (out["alpha"].cpu().double() - ref).abs().max().item()
-    assert err <= 2e-5, err
+    assert err <= (1.5e-6 if B == 1 else 5e-6), err
 
 
 @pytest.mark.parametrize("dtype,rows", [("bf16", 1), ("bf16", 511), ("bf16", 512), ("f16", 3),
