@@ -1375,22 +1375,34 @@ int launch_t(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* learned) {
 }
 
 // Argmax and agreement by the team kernel where it is the faster, or the streaming kernel cannot number
-// the call's units (*taken), else nothing. The streaming
-// kernel is, also for the smallest calls, where a group has few units (at most 20: 64 queries x 8
-// drafters x 8 positions x 4000 bf16 logits 15.7 us, by teams 27.6) or teams would claim items beyond
-// their two fixed ones (us, streaming and teams, at items per resident workgroup: 16 x 5 x 7 x 50257
-// 17.9 and 47.4 at 2.2, 64 x 4 x 4 x 32000 21.4 and 42.6 at 2.7, 24 x 8 x 6 x 128256 63 and 76 at
-// 7.1). Below that its waves, which all count their arrival at their group's word, cost more than they
-// stream: 1 x 8 x 8 x 151936 46 and 10.3, 12 x 5 x 7 x 50257 32 and 19.5 at 1.6; with more than 62 of
-// them to a group up to about six items (6 x 8 x 6 x 128256 fp32 68 and 39 at 3.5, 8 53 and 49.5 at
-// 4.7, 12 58 and 78 at 7.1).
+// the call's units (*taken), else nothing. The streaming kernel's waves all count their arrival at their
+// group's word, which costs little where a group has few waves (wpg) or each wave a long span, as its
+// arrivals then spread over the run; teams cost a hop per item, and more where they claim items beyond
+// their two fixed ones. us, streaming and by teams:
+// - groups of few units or rows of few slices, streaming: 62 queries x 8 drafters x 8 positions x 4050 bf16
+//   logits 19.6 and 30.3, 15 x 11 x 1 x 4913 (3 slices) 8.7 and 11.2; 21 x 8 x 6 x 9749 (5) 37.0 and 20.6,
+//   9 x 43 x 9 x 8032 (4, and 88 units) 59.6 and 31.5;
+// - up to two items per team, teams: 1 x 8 x 8 x 151936 46 and 10.3, 1 x 15 x 8 x 96771 197 and 14.4,
+//   23 x 8 x 3 x 33784 fp32 48 and 25.6 at 1.8; with groups of up to 25 waves, up to one and a half:
+//   42 x 4 x 2 x 42365 28.1 and 21.4 at 1.2, 21 x 6 x 6 x 40445 25.1 and 29.4 at 2;
+// - up to six, with more than 50 waves to a group of at most four units each and up to 128 row sets, which
+//   are claimed one by one: 10 x 6 x 3 x 151133 fp32 119 and 41, 8 x 9 x 8 x 62503 (128) 77 and 65; 24 x 17 x 2
+//   x 37314 (144) 30.4 and 57.2, 13 x 10 x 5 x 52015 (48 waves) 44.3 and 59.7, 1 x 52 x 24 x 71662
+//   (six units) 55.5 and 91, 5 x 42 x 8 x 43670 (five) 52.4 and 99.6; with longer spans where row sets are
+//   few: 10 x 7 x 4 x 125874 fp32 (40 sets) 73.6 and 46.7, 1 x 8 x 48 x 128496 fp32 (48) 59.4 and 57.5, 8 x
+//   15 x 5 x 101752 fp32 (80) 65.6 and 73.6; and with more than 200 waves to a group: 3 x 63 x 6 x 51371 101
+//   and 58, 5 x 47 x 3 x 83876 fp32 71 and 66.
 template <int DT, int D>
 int launch_team_argmax(TeamArgs A, const TeamGeom& g, hipStream_t stream, bool* taken) {
   static std::atomic<int> cached[64];
   const int cap = capacity_of(hs_team_argmax_kernel<DT, D>, cached);
   const ArgmaxPlan p = argmax_plan(g);
   const int64_t sets = g.items / g.S, teams = std::min<int64_t>({cap / g.S, sets, (int64_t)kMaxTeams});
-  const bool faster = p.per_group > 20 && sets <= (p.per_group <= 62 * p.span ? 2 : 6) * teams;
+  const auto wpg_over = [&](int64_t waves) { return p.per_group > waves * p.span; };
+  const bool many = wpg_over(200) ||
+                    (p.span <= 4 ? wpg_over(50) && sets <= 128 : wpg_over(62) && sets <= 48);
+  const bool faster = p.per_group > 20 && (g.S > 4 || p.per_group > 56) &&
+                      2 * sets <= (many ? 12 : wpg_over(25) ? 4 : 3) * teams;
   *taken = !argmax_fits(p) || (teams > 0 && faster);
   if (!*taken) return HS_OK;
   if (teams <= 0) return HS_ERR_LIMIT;

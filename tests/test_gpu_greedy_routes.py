@@ -1,7 +1,8 @@
 """Greedy calls on both sides of the line between the team kernel and the streaming argmax kernel:
-groups of few and of many units, teams with at most two items, with up to six and with more, rows
-that end inside a vector, slices and units that end inside a row. Argmaxes and agreements are whole
-numbers: exact. Interleaved on one workspace with calls that need alpha."""
+groups of few and of many units and waves, few and many row sets, teams with at most two items, with
+up to six and with more, rows of few slices, rows that end inside a vector, slices and units that end
+inside a row. Argmaxes and agreements are whole numbers: exact. Interleaved on one workspace with
+calls that need alpha."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +25,8 @@ def reference(x, V):
 
 @pytest.mark.parametrize("dtype", list(DTYPES))
 @pytest.mark.parametrize("N,K,V", [(8, 3, 20489), (5, 7, 50257), (1, 4, 8200), (20, 3, 30001),
-                                   (3, 2, 4097), (8, 8, 4000)])
+                                   (3, 2, 4097), (8, 8, 4000), (17, 2, 37314), (47, 3, 33001),
+                                   (43, 9, 8032)])
 def test_greedy_over_the_batch_sizes(N, K, V, dtype):
     for B in (1, 2, 5, 12, 17, 33):
         ld = (V + 7) // 8 * 8
